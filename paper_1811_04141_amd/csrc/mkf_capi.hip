@@ -126,7 +126,7 @@ struct mkf_ctx {
   int64_t n_seeds_ok = 0;
 
   // find
-  DevBuf d_cand, d_fin_key, d_fin_rec, d_fin_meta, d_bp, d_steps, d_tiles, d_qoff;
+  DevBuf d_cand, d_fin_key, d_fin_rec, d_fin_meta, d_bp, d_qoff;
   DevBuf d_out;  // result rows (kOut*), n_seeds words each
   hipEvent_t ev_a = nullptr, ev_b = nullptr, ev_m0 = nullptr, ev_m1 = nullptr;
   hipGraph_t graph = nullptr;
@@ -153,7 +153,7 @@ struct mkf_ctx {
                      &d_byorig, &d_bad, &d_seed_event, &d_seed_hits, &d_seed_state, &d_seed_ok,
                      &d_plan_len, &d_plan, &d_plan_l, &d_order, &d_pstate, &d_pinfo,
                      &d_pevent, &d_pplan, &d_cand, &d_fin_key, &d_fin_rec, &d_fin_meta,
-                     &d_bp, &d_steps, &d_tiles, &d_qoff, &d_out, &d_mlp_param, &d_mlp_m, &d_mlp_v, &d_W1p,
+                     &d_bp, &d_qoff, &d_out, &d_mlp_param, &d_mlp_m, &d_mlp_v, &d_W1p,
                      &d_W2p, &d_W3p, &d_W2T, &d_W3T, &d_mb1, &d_mb2, &d_mb3, &d_cnt, &d_radii,
                      &d_tx, &d_tt, &d_tvalid, &d_partial, &d_partial2, &d_loss, &d_grad, &d_bf_tmp, &d_sm_wk, &d_sm_n, &d_tr_cnt, &d_tr_off, &d_tr_tmp, &d_dup_h, &d_dup_n, &d_dup_cnt, &d_dup_off,
                      &d_dup_fill, &d_dup_list, &d_dup_tmp, &d_dup_total, &d_seed_chi2};
@@ -241,14 +241,16 @@ FindParams params(mkf_ctx *c) {
   P.fin_rec = c->d_fin_rec.as<float>();
   P.fin_meta = c->d_fin_meta.as<int>();
   P.bp = c->d_bp.as<int>();
-  P.tile_counter = c->d_tiles.as<int>();
+  // one allocation, cleared by one fill: step count, counters, tile counters
+  unsigned long long *clear = c->d_cnt.as<unsigned long long>();
+  P.tile_counter = reinterpret_cast<int *>(clear + kTileWord0);
   P.q_off = c->d_qoff.as<int64_t>();
   P.max_plan = c->max_plan_len;
-  P.n_steps = c->d_steps.as<unsigned long long>();
+  P.n_steps = clear;
   P.mlp = MlpWeights{c->d_W1p.as<__bf16>(), c->d_W2p.as<__bf16>(), c->d_W3p.as<__bf16>(),
                      c->d_W2T.as<__bf16>(), c->d_W3T.as<__bf16>(), c->d_mb1.as<float>(),
                      c->d_mb2.as<float>(), c->d_mb3.as<float>()};
-  P.counters = c->d_cnt.as<unsigned long long>();
+  P.counters = clear + 1;
   return P;
 }
 
@@ -286,7 +288,7 @@ hipError_t mlp_setup(mkf_ctx *c) {
   if (e == hipSuccess) e = c->d_mb1.ensure(sizeof(float) * 64);
   if (e == hipSuccess) e = c->d_mb2.ensure(sizeof(float) * 64);
   if (e == hipSuccess) e = c->d_mb3.ensure(sizeof(float) * 32);
-  if (e == hipSuccess) e = c->d_cnt.ensure(sizeof(unsigned long long) * kCounters * kCounterSlots);
+  if (e == hipSuccess) e = c->d_cnt.ensure(sizeof(unsigned long long) * kClearWords);
   if (e != hipSuccess) return e;
   DevBuf *zero[] = {&c->d_mlp_m, &c->d_mlp_v, &c->d_W1p, &c->d_W2p, &c->d_W3p, &c->d_W2T,
                     &c->d_W3T, &c->d_mb1, &c->d_mb2, &c->d_mb3, &c->d_cnt};
@@ -371,13 +373,10 @@ mkf_status mkf_create(const mkf_config *cfg, void *stream, mkf_ctx **out) {
   if (e == hipSuccess) e = hipEventCreate(&c->ev_b);
   if (e == hipSuccess) e = hipEventCreate(&c->ev_m0);
   if (e == hipSuccess) e = hipEventCreate(&c->ev_m1);
-  if (e == hipSuccess) e = c->d_steps.ensure(sizeof(unsigned long long));
-  if (e == hipSuccess) e = c->d_tiles.ensure(sizeof(int) * kQueues);
   if (e == hipSuccess) e = c->d_bad.ensure(sizeof(int));
   if (e == hipSuccess)
     e = hipHostMalloc(reinterpret_cast<void **>(&c->h_cnt),
-                      sizeof(unsigned long long) * (1 + kCounters * kCounterSlots),
-                      hipHostMallocDefault);
+                      sizeof(unsigned long long) * kFindWords, hipHostMallocDefault);
   if (e != hipSuccess) {
     delete c;
     return fail(nullptr, MKF_E_HIP, "HIP setup failed: %s", hipGetErrorString(e));
@@ -875,12 +874,9 @@ mkf_status mkf_get_seed_states(mkf_ctx *c, float *par, float *cov, int32_t *ok,
 // null) bracket the layer-step kernels.
 static int enqueue_find(mkf_ctx *c, const FindParams &P, hipEvent_t main_a, hipEvent_t main_b) {
   int launches = 0;
-  launch_fill_u64(c->stream, c->d_steps.as<unsigned long long>(), 1, 0ull);
-  launch_fill_u64(c->stream, c->d_cnt.as<unsigned long long>(), kCounters * kCounterSlots, 0ull);
+  launch_fill_u64(c->stream, c->d_cnt.as<unsigned long long>(), kClearWords, 0ull);
   ++launches;
   if (c->cfg.flags & MKF_F_BATCHED) {
-    launch_fill_i32(c->stream, c->d_tiles.as<int>(), kQueues, 0);
-    ++launches;
     if (main_a) (void)hipEventRecord(main_a, c->stream);
     launch_find_persistent(c->stream, P, c->tuning.blocks_per_cu * c->n_cu,
                            c->tuning.waves_per_simd, (c->cfg.flags & MKF_F_SURROGATE) != 0,
@@ -940,13 +936,10 @@ mkf_status mkf_find(mkf_ctx *c) {
     launch_check_results(c->stream, P);
     HIP_TRY(c, hipGetLastError());
   }
-  // the step count and counters: two copies into pinned memory behind the
+  // the step count and counters: one copy into pinned memory behind the
   // find on its stream, then one wait, which also completes the events
-  unsigned long long *cnt = c->h_cnt + 1;
-  HIP_TRY(c, hipMemcpyAsync(c->h_cnt, c->d_steps.ptr, sizeof(unsigned long long),
-                            hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(cnt, c->d_cnt.ptr,
-                            sizeof(unsigned long long) * kCounters * kCounterSlots,
+  const unsigned long long *cnt = c->h_cnt + 1;
+  HIP_TRY(c, hipMemcpyAsync(c->h_cnt, c->d_cnt.ptr, sizeof(unsigned long long) * kFindWords,
                             hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   float ms = 0.f, mms = -1.f;

@@ -82,8 +82,10 @@ struct FindParams {
   int *bp;                  // [kMaxPlan][n_seeds][slots] back-pointers
   // persistent form: kQueues tile queues, queue q owning positions
   // [q_off[q], q_off[q+1]) (whole events); the blocks of XCD x start on
-  // queue x and move on to the others when it is empty
-  int *tile_counter;        // [kQueues]
+  // queue x and move on to the others when it is empty.  The queues' counters
+  // of tiles handed out lie kTilePad words apart, each in a cache line of its
+  // own.
+  int *tile_counter;        // [kQueues][kTilePad]
   const int64_t *q_off;     // [kQueues + 1]
   int max_plan;             // longest layer plan (sizes the persistent form's LDS records)
   unsigned long long *n_steps;
@@ -97,8 +99,15 @@ struct FindParams {
   // not queue on one address; the host sums the slots
   unsigned long long *counters;
 };
+constexpr int kTilePad = 32;
 constexpr int kCounters = 6;
 constexpr int kCounterSlots = 64;
+// what a find clears before it starts, one allocation (64-bit words): the
+// step count, the counters, then (in cache lines of their own) the tile
+// counters
+constexpr int kFindWords = 1 + kCounters * kCounterSlots;
+constexpr int kTileWord0 = (kFindWords + 15) / 16 * 16;
+constexpr int kClearWords = kTileWord0 + kQueues * kTilePad / 2;
 enum {
   kCntSurKept = 0, kCntSurRejected = 1, kCntNearCut = 2, kCntRk = 3, kCntNewton = 4,
   kCntCheckFailed = 5  // result records that fail the checked find's invariants
