@@ -15,6 +15,7 @@
 //  finalize    : best candidate per seed, hit history from back-pointers
 //  propagate / fit : unit propagation and search-free Kalman fitting.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 
 #include "mkf_kernels.hpp"
 
@@ -1014,11 +1015,12 @@ __global__ __launch_bounds__(256, kWaves) void k_find_persistent_mat(FindParams 
 // Gather the seed results into processing order (untimed preparation), so
 // that every read of the find is by position.
 __global__ __launch_bounds__(256) void k_permute_seeds(FindParams P, float *pstate, int *pinfo,
-                                                       int *pevent, int8_t *pplan) {
+                                                       int *pevent, int8_t *pplan, int *pos_of) {
   const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (pos >= P.n_seeds) return;
   const size_t N = (size_t)P.n_seeds;
   const int seed = P.order[pos];
+  pos_of[seed] = (int)pos;
   for (int i = 0; i < 27; ++i) pstate[(size_t)pos * kSeedWords + i] = P.seed_state[i * N + seed];
   // the last word: the index of the event's first hit (below 2^31), read
   // with the state so that the find need not look it up
@@ -1027,6 +1029,50 @@ __global__ __launch_bounds__(256) void k_permute_seeds(FindParams P, float *psta
   pevent[pos] = P.seed_event[seed];
   for (int s = 0; s < kMaxPlan; ++s)
     pplan[(size_t)pos * kMaxPlan + s] = P.plan[(size_t)seed * kMaxPlan + s];
+}
+
+// The caller's track records, in seed order, written by the device straight
+// into pinned host memory: one lane per 32-bit word, so that a wavefront reads
+// words of one result row and writes 256 contiguous bytes.  Bound by the link
+// to the host: 46 GB/s with the host's copies behind it, of the 57 GB/s that a
+// plain copy to pinned memory reaches.
+__global__ __launch_bounds__(256) void k_tracks(FindParams P, const int *pos_of, int64_t first,
+                                                int64_t n, int *out) {
+  static_assert(offsetof(mkf_track, par) == 24 && offsetof(mkf_track, cov) == 48 &&
+                offsetof(mkf_track, plan) == 132 && offsetof(mkf_track, hit) == 164 &&
+                sizeof(mkf_track) == 292, "record layout");
+  constexpr int kPar = 6, kPlan = 33, kHit = 41;  // words
+  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = id / kTrackWords;
+  const int w = (int)(id - i * kTrackWords);
+  if (i >= n) return;
+  const int seed = (int)(first + i);
+  const int64_t pos = pos_of[seed];
+  const int *row = reinterpret_cast<const int *>(P.out + (size_t)pos * kOutWords);
+  const int info = P.pinfo[pos];
+  const int ok = (info >> 8) & 1, plen = ok ? info & 0xFF : 0;
+  int v;
+  if (w >= kHit) {
+    v = w - kHit < plen ? row[kOutHit + w - kHit] : MKF_HIT_NONE;
+  } else if (w >= kPlan) {
+    const int k = 4 * (w - kPlan);  // four layer ids, those past the plan's end -1
+    v = -1;
+    if (k < plen) {
+      v = reinterpret_cast<const int *>(P.pplan + (size_t)pos * kMaxPlan)[w - kPlan];
+      if (plen - k < 4) v |= (int)(~0u << (8 * (plen - k)));
+    }
+  } else if (w >= kPar) {
+    v = row[kOutPar + w - kPar];  // (cov follows par in both)
+  } else if (w == 5) {
+    v = row[kOutChi2];
+  } else if (w == 4) {
+    v = plen;
+  } else if (w >= 2) {
+    v = (row[kOutMeta] >> (w == 2 ? 0 : 8)) & 0xFF;
+  } else {
+    v = w == 1 ? ok : seed;
+  }
+  out[id] = v;
 }
 
 // --------------------------------------------------------------- seeding
@@ -2420,10 +2466,17 @@ void launch_check_results(hipStream_t s, const FindParams &P) {
 }
 
 void launch_permute_seeds(hipStream_t s, const FindParams &P, float *pstate, int *pinfo,
-                          int *pevent, int8_t *pplan) {
+                          int *pevent, int8_t *pplan, int *pos_of) {
   if (P.n_seeds == 0) return;
   hipLaunchKernelGGL(k_permute_seeds, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P,
-                     pstate, pinfo, pevent, pplan);
+                     pstate, pinfo, pevent, pplan, pos_of);
+}
+
+void launch_tracks(hipStream_t s, const FindParams &P, const int *pos_of, int64_t first, int64_t n,
+                   int *out) {
+  if (n == 0) return;
+  hipLaunchKernelGGL(k_tracks, dim3(blocks_for(n * kTrackWords, 256)), dim3(256), 0, s, P, pos_of,
+                     first, n, out);
 }
 
 void launch_propagate(hipStream_t s, const FindParams &P, int64_t n, const float *par,

@@ -165,7 +165,12 @@ void launch_seed(hipStream_t s, const FindParams &P, const int *seed_hits, float
                  int *seed_ok, int *plan_len, int8_t *plan, double *plan_l, float *seed_chi2,
                  const DevRegion *regions, int n_regions);
 void launch_permute_seeds(hipStream_t s, const FindParams &P, float *pstate, int *pinfo,
-                          int *pevent, int8_t *pplan);
+                          int *pevent, int8_t *pplan, int *pos_of);
+// mkf_track records of seeds first .. first + n - 1 into out (kTrackWords
+// words each; host memory the device can write, or device memory)
+constexpr int kTrackWords = (int)sizeof(mkf_track) / 4;
+void launch_tracks(hipStream_t s, const FindParams &P, const int *pos_of, int64_t first, int64_t n,
+                   int *out);
 void launch_find_init(hipStream_t s, const FindParams &P);
 void launch_find_step(hipStream_t s, const FindParams &P, int step, int64_t n_active_seeds);
 // group: lanes per seed (6 or 8; 8 whenever the candidate budget exceeds 6)
