@@ -125,8 +125,9 @@ struct mkf_ctx {
 
   // seeds
   int64_t n_seeds = 0;
-  DevBuf d_seed_event, d_seed_hits, d_seed_state, d_seed_ok, d_plan_len, d_plan, d_plan_l;
+  DevBuf d_seed_event, d_seed_hits, d_seed_state, d_seed_ok, d_plan_len, d_plan;
   DevBuf d_seed_chi2;
+  DevBuf d_cell_counts, d_cell_start, d_cell_rank;  // the processing order's counting sort
   DevBuf d_order, d_pos, d_pstate, d_pinfo, d_pevent, d_pplan;
   DevBuf d_bf_tmp;  // backward fit: state between its FP64 and FP32 parts
   DevBuf d_sm_wk, d_sm_n;  // smoothing: forward-pass states per surface, surface counts
@@ -137,7 +138,7 @@ struct mkf_ctx {
   int64_t n_seeds_ok = 0;
 
   // find
-  DevBuf d_cand, d_fin_key, d_fin_rec, d_fin_meta, d_bp, d_qoff;
+  DevBuf d_cand, d_fin_key, d_fin_rec, d_fin_meta, d_bp;
   DevBuf d_out;  // result rows (kOut*), n_seeds words each
   hipEvent_t ev_a = nullptr, ev_b = nullptr, ev_m0 = nullptr, ev_m1 = nullptr;
   hipGraph_t graph = nullptr;
@@ -147,6 +148,8 @@ struct mkf_ctx {
   // pinned host words the find's step count and counters are read back
   // into: [0] steps, then kCounters x kCounterSlots
   unsigned long long *h_cnt = nullptr;
+  int *h_len = nullptr;  // pinned: the seeds' counts by plan length
+  int *h_bad = nullptr;  // pinned: set by the device where an input is out of range
   // pinned slots that the track records pass through on their way to the
   // caller (mkf_get_tracks), and an event for each
   mkf_track *h_tracks = nullptr;
@@ -167,9 +170,9 @@ struct mkf_ctx {
     DevBuf *all[] = {&d_layers, &d_regions, &d_mat, &d_ev_off, &d_x, &d_y, &d_z, &d_vu, &d_vv, &d_layer,
                      &d_hit_bin, &d_counts, &d_fill, &d_bin_start, &d_scan_tmp, &d_sorted,
                      &d_byorig, &d_bad, &d_seed_event, &d_seed_hits, &d_seed_state, &d_seed_ok,
-                     &d_plan_len, &d_plan, &d_plan_l, &d_order, &d_pos, &d_pstate, &d_pinfo,
+                     &d_plan_len, &d_plan, &d_cell_counts, &d_cell_start, &d_cell_rank, &d_order, &d_pos, &d_pstate, &d_pinfo,
                      &d_pevent, &d_pplan, &d_cand, &d_fin_key, &d_fin_rec, &d_fin_meta,
-                     &d_bp, &d_qoff, &d_out, &d_mlp_param, &d_mlp_m, &d_mlp_v, &d_W1p,
+                     &d_bp, &d_out, &d_mlp_param, &d_mlp_m, &d_mlp_v, &d_W1p,
                      &d_W2p, &d_W3p, &d_W2T, &d_W3T, &d_mb1, &d_mb2, &d_mb3, &d_cnt, &d_radii,
                      &d_tx, &d_tt, &d_tvalid, &d_partial, &d_partial2, &d_loss, &d_grad, &d_bf_tmp, &d_sm_wk, &d_sm_n, &d_tr_cnt, &d_tr_off, &d_tr_tmp, &d_dup_h, &d_dup_n, &d_dup_cnt, &d_dup_off,
                      &d_dup_fill, &d_dup_list, &d_dup_tmp, &d_dup_total, &d_seed_chi2};
@@ -180,7 +183,7 @@ struct mkf_ctx {
     if (ev_b) (void)hipEventDestroy(ev_b);
     if (ev_m0) (void)hipEventDestroy(ev_m0);
     if (ev_m1) (void)hipEventDestroy(ev_m1);
-    if (h_cnt) (void)hipHostFree(h_cnt);
+    if (h_cnt) (void)hipHostFree(h_cnt);  // (h_len and h_bad lie behind it)
     if (h_tracks) (void)hipHostFree(h_tracks);
     for (hipEvent_t e : ev_copy)
       if (e) (void)hipEventDestroy(e);
@@ -263,7 +266,6 @@ FindParams params(mkf_ctx *c) {
   // one allocation, cleared by one fill: step count, counters, tile counters
   unsigned long long *clear = c->d_cnt.as<unsigned long long>();
   P.tile_counter = reinterpret_cast<int *>(clear + kTileWord0);
-  P.q_off = c->d_qoff.as<int64_t>();
   P.max_plan = c->max_plan_len;
   P.n_steps = clear;
   P.mlp = MlpWeights{c->d_W1p.as<__bf16>(), c->d_W2p.as<__bf16>(), c->d_W3p.as<__bf16>(),
@@ -395,11 +397,15 @@ mkf_status mkf_create(const mkf_config *cfg, void *stream, mkf_ctx **out) {
   if (e == hipSuccess) e = c->d_bad.ensure(sizeof(int));
   if (e == hipSuccess)
     e = hipHostMalloc(reinterpret_cast<void **>(&c->h_cnt),
-                      sizeof(unsigned long long) * kFindWords, hipHostMallocDefault);
+                      sizeof(unsigned long long) * kFindWords +
+                          sizeof(int) * (kLenSlots * kLenWords + 1),
+                      hipHostMallocDefault);
   if (e != hipSuccess) {
     delete c;
     return fail(nullptr, MKF_E_HIP, "HIP setup failed: %s", hipGetErrorString(e));
   }
+  c->h_len = reinterpret_cast<int *>(c->h_cnt + kFindWords);
+  c->h_bad = c->h_len + kLenSlots * kLenWords;
   int dev = 0, n_cu = 0;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
@@ -489,7 +495,7 @@ mkf_status build_index(mkf_ctx *c) {
   HIP_TRY(c, c->d_counts.ensure(sizeof(int) * (size_t)std::max<int64_t>(total_bins, 1)));
   HIP_TRY(c, c->d_fill.ensure(sizeof(int) * (size_t)std::max<int64_t>(total_bins, 1)));
   HIP_TRY(c, c->d_bin_start.ensure(sizeof(int) * (size_t)(total_bins + 1)));
-  HIP_TRY(c, c->d_scan_tmp.ensure(sizeof(int) * (size_t)(4 * (total_bins / 2048 + 4) + 64)));
+  HIP_TRY(c, c->d_scan_tmp.ensure(sizeof(int) * (size_t)scan_tmp_words(total_bins)));
   HIP_TRY(c, c->d_sorted.ensure(sizeof(HitRec) * (size_t)(std::max<int64_t>(n_hits, 1) + kHitPad)));
   HIP_TRY(c, c->d_byorig.ensure(sizeof(HitRec) * (size_t)std::max<int64_t>(n_hits, 1)));
   HIP_TRY(c, hipEventRecord(c->ev_a, c->stream));
@@ -499,7 +505,7 @@ mkf_status build_index(mkf_ctx *c) {
   launch_hit_bins(c->stream, P, n_hits, c->d_layer.as<int>(), c->d_hit_bin.as<int>(),
                   c->d_counts.as<int>());
   launch_scan(c->stream, c->d_counts.as<int>(), c->d_bin_start.as<int>(), total_bins,
-              c->d_scan_tmp.as<int>(), nullptr);
+              c->d_scan_tmp.as<int>());
   launch_scatter(c->stream, P, n_hits, c->d_hit_bin.as<int>(), c->d_fill.as<int>(),
                  c->d_sorted.as<HitRec>(), c->d_byorig.as<HitRec>());
   HIP_TRY(c, hipGetLastError());
@@ -716,144 +722,118 @@ mkf_status mkf_seed(mkf_ctx *c, int64_t n_seeds, const int32_t *seed_event,
   if (n_seeds < 0 || n_seeds >= ((int64_t)1 << 28)) return fail(c, MKF_E_ARG, "bad seed count");
   if (n_seeds > 0 && (!seed_event || !seed_hits)) return fail(c, MKF_E_ARG, "seed array is NULL");
   if (mem != MKF_MEM_HOST && mem != MKF_MEM_DEVICE) return fail(c, MKF_E_ARG, "bad mem");
-  std::vector<int32_t> h_ev, h_hits;
-  const int32_t *sev = seed_event, *sh = seed_hits;
+  const size_t N = (size_t)std::max<int64_t>(n_seeds, 1);
   if (mem == MKF_MEM_DEVICE && n_seeds > 0) {
-    // seeds are small: validate on the host
-    h_ev.resize(n_seeds);
-    h_hits.resize(3 * n_seeds);
-    HIP_TRY(c, hipMemcpyAsync(h_ev.data(), seed_event, 4 * n_seeds, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(h_hits.data(), seed_hits, 12 * n_seeds, hipMemcpyDeviceToHost, c->stream));
+    FindParams V = params(c);
+    V.n_seeds = n_seeds;
+    *c->h_bad = 0;
+    launch_validate_seeds(c->stream, V, seed_event, seed_hits, c->h_bad);
+    HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    sev = h_ev.data();
-    sh = h_hits.data();
   }
-  for (int64_t i = 0; i < n_seeds; ++i) {
-    if (sev[i] < 0 || sev[i] >= c->n_events)
-      return fail(c, MKF_E_ARG, "seed %lld: event %d out of range", (long long)i, sev[i]);
-    const int64_t nh = c->ev_off[sev[i] + 1] - c->ev_off[sev[i]];
-    for (int k = 0; k < 3; ++k)
-      if (sh[3 * i + k] < 0 || sh[3 * i + k] >= nh)
-        return fail(c, MKF_E_ARG, "seed %lld: hit index out of range", (long long)i);
+  if (mem == MKF_MEM_HOST || (n_seeds > 0 && *c->h_bad)) {
+    // host arrays, or device arrays with an index out of range: the first one
+    std::vector<int32_t> h_ev, h_hits;
+    const int32_t *sev = seed_event, *sh = seed_hits;
+    if (mem == MKF_MEM_DEVICE) {
+      h_ev.resize(n_seeds);
+      h_hits.resize(3 * n_seeds);
+      HIP_TRY(c, hipMemcpyAsync(h_ev.data(), seed_event, 4 * n_seeds, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(c, hipMemcpyAsync(h_hits.data(), seed_hits, 12 * n_seeds, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(c, hipStreamSynchronize(c->stream));
+      sev = h_ev.data();
+      sh = h_hits.data();
+    }
+    for (int64_t i = 0; i < n_seeds; ++i) {
+      if (sev[i] < 0 || sev[i] >= c->n_events)
+        return fail(c, MKF_E_ARG, "seed %lld: event %d out of range", (long long)i, sev[i]);
+      const int64_t nh = c->ev_off[sev[i] + 1] - c->ev_off[sev[i]];
+      for (int k = 0; k < 3; ++k)
+        if (sh[3 * i + k] < 0 || sh[3 * i + k] >= nh)
+          return fail(c, MKF_E_ARG, "seed %lld: hit index out of range", (long long)i);
+    }
   }
   c->stage = kHits;
   drop_graph(c);
-  const size_t N = (size_t)std::max<int64_t>(n_seeds, 1);
-  mkf_status st;
-  if ((st = stage_in(c, c->d_seed_event, sev, 4 * (size_t)n_seeds, MKF_MEM_HOST))) return st;
-  if ((st = stage_in(c, c->d_seed_hits, sh, 12 * (size_t)n_seeds, MKF_MEM_HOST))) return st;
+  const bool batched = (c->cfg.flags & MKF_F_BATCHED) != 0;
+  // cells of the processing order: no more than a few per seed
+  SeedCells cells{0, std::max(1, c->n_events), batched ? 0 : 1};
+  while (cells.n_groups > 1 && cells.cells() > std::max<int64_t>(1 << 16, 4 * n_seeds)) {
+    ++cells.event_shift;
+    cells.n_groups = (int)(((int64_t)c->n_events + ((int64_t)1 << cells.event_shift) - 1) >>
+                           cells.event_shift);
+  }
+  const int64_t n_cells = cells.cells(), n_len = kLenSlots * kLenWords;
   HIP_TRY(c, c->d_seed_event.ensure(4 * N));
-  HIP_TRY(c, c->d_seed_state.ensure(sizeof(float) * 27 * N));
+  HIP_TRY(c, c->d_seed_hits.ensure(12 * N));
+  HIP_TRY(c, c->d_seed_state.ensure(sizeof(float) * kSeedWords * N));
   HIP_TRY(c, c->d_seed_ok.ensure(4 * N));
   HIP_TRY(c, c->d_plan_len.ensure(4 * N));
   HIP_TRY(c, c->d_plan.ensure(kMaxPlan * N));
-  HIP_TRY(c, c->d_plan_l.ensure(sizeof(double) * kMaxPlan * N));
-  HIP_TRY(c, c->d_order.ensure(4 * N));
   HIP_TRY(c, c->d_seed_chi2.ensure(4 * N));
-  c->n_seeds = n_seeds;
-  FindParams P = params(c);
-  HIP_TRY(c, hipEventRecord(c->ev_a, c->stream));
-  launch_seed(c->stream, P, c->d_seed_hits.as<int>(), c->d_seed_state.as<float>(),
-              c->d_seed_ok.as<int>(), c->d_plan_len.as<int>(), c->d_plan.as<int8_t>(),
-              c->d_plan_l.as<double>(), c->d_seed_chi2.as<float>(),
-              c->n_regions > 0 ? c->d_regions.as<DevRegion>() : nullptr, c->n_regions);
-  HIP_TRY(c, hipGetLastError());
-  HIP_TRY(c, hipEventRecord(c->ev_b, c->stream));
-  // processing order: longest plans first (the persistent form takes tiles
-  // in this order, so the longest work starts first), then by event and
-  // direction so that a wavefront's seeds search nearby hits
-  std::vector<int32_t> plen(n_seeds), ok(n_seeds), ev(sev, sev + n_seeds);
-  std::vector<float> phi(n_seeds), theta(n_seeds);
-  if (n_seeds > 0) {
-    HIP_TRY(c, hipMemcpyAsync(plen.data(), c->d_plan_len.ptr, 4 * n_seeds, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(ok.data(), c->d_seed_ok.ptr, 4 * n_seeds, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(phi.data(), c->d_seed_state.as<float>() + 4 * N, 4 * n_seeds,
-                              hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(theta.data(), c->d_seed_state.as<float>() + 5 * N, 4 * n_seeds,
-                              hipMemcpyDeviceToHost, c->stream));
-  }
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  float ms = 0.f;
-  HIP_TRY(c, hipEventElapsedTime(&ms, c->ev_a, c->ev_b));
-  c->stats.seed_ms = ms;
-  std::vector<int32_t> order(n_seeds);
-  std::iota(order.begin(), order.end(), 0);
-  int64_t q_off[kQueues + 1] = {};
-  if (c->cfg.flags & MKF_F_BATCHED) {
-    // whole events to the kQueues tile queues (one per XCD), balanced by
-    // their summed plan lengths (longest first to the least loaded queue);
-    // inside a queue event by event, longest plans first, then direction
-    std::vector<int64_t> cost(c->n_events, 0);
-    for (int64_t i = 0; i < n_seeds; ++i) cost[ev[i]] += plen[i] + 1;
-    std::vector<int> evs(c->n_events), ev_q(c->n_events, 0);
-    std::iota(evs.begin(), evs.end(), 0);
-    std::stable_sort(evs.begin(), evs.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-    int64_t load[kQueues] = {};
-    for (int e : evs) {
-      int q = 0;
-      for (int k = 1; k < kQueues; ++k)
-        if (load[k] < load[q]) q = k;
-      ev_q[e] = q;
-      load[q] += cost[e];
-    }
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-      if (ev_q[ev[a]] != ev_q[ev[b]]) return ev_q[ev[a]] < ev_q[ev[b]];
-      if (ev[a] != ev[b]) return ev[a] < ev[b];
-      if (plen[a] != plen[b]) return plen[a] > plen[b];
-      const int ta = (int)(theta[a] * 8.f), tb = (int)(theta[b] * 8.f);
-      if (ta != tb) return ta < tb;
-      return phi[a] < phi[b];
-    });
-    for (int64_t p = 0; p < n_seeds; ++p) q_off[ev_q[ev[order[p]]] + 1]++;
-    for (int q = 0; q < kQueues; ++q) q_off[q + 1] += q_off[q];
-  } else {
-    // longest plans first, so the seeds still active at a step form a prefix
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-      if (plen[a] != plen[b]) return plen[a] > plen[b];
-      if (ev[a] != ev[b]) return ev[a] < ev[b];
-      const int ta = (int)(theta[a] * 8.f), tb = (int)(theta[b] * 8.f);
-      if (ta != tb) return ta < tb;
-      return phi[a] < phi[b];
-    });
-    for (int q = 1; q <= kQueues; ++q) q_off[q] = n_seeds;
-  }
-  HIP_TRY(c, c->d_qoff.ensure(sizeof(q_off)));
-  HIP_TRY(c, hipMemcpyAsync(c->d_qoff.ptr, q_off, sizeof(q_off), hipMemcpyHostToDevice, c->stream));
-  if (n_seeds > 0)
-    HIP_TRY(c, hipMemcpyAsync(c->d_order.ptr, order.data(), 4 * n_seeds, hipMemcpyHostToDevice, c->stream));
-  c->max_plan_len = 0;
-  c->n_seeds_ok = 0;
-  for (int64_t i = 0; i < n_seeds; ++i) {
-    c->max_plan_len = std::max(c->max_plan_len, plen[i]);
-    c->n_seeds_ok += ok[i] ? 1 : 0;
-  }
-  c->active_at_step.assign(kMaxPlan, 0);
-  for (int s = 0; s < kMaxPlan; ++s) {
-    // the layer-synchronous form keeps the longest plans first: the seeds
-    // still active at step s form a prefix of the positions
-    int64_t n = 0;
-    for (int64_t i = 0; i < n_seeds; ++i) n += plen[i] > s ? 1 : 0;
-    c->active_at_step[s] = (c->cfg.flags & MKF_F_BATCHED) ? n_seeds : n;
-  }
-  // find buffers
-  HIP_TRY(c, c->d_cand.ensure(sizeof(float) * kCandFields * kGroup * N));
-  HIP_TRY(c, c->d_fin_key.ensure(8 * N));
-  HIP_TRY(c, c->d_fin_rec.ensure(sizeof(float) * 28 * N));
-  HIP_TRY(c, c->d_fin_meta.ensure(4 * N));
-  HIP_TRY(c, c->d_bp.ensure(4 * (size_t)kMaxPlan * kGroup * N));
+  HIP_TRY(c, c->d_cell_counts.ensure(sizeof(int) * (size_t)(n_cells + n_len)));
+  HIP_TRY(c, c->d_cell_start.ensure(sizeof(int) * (size_t)(n_cells + 1)));
+  HIP_TRY(c, c->d_cell_rank.ensure(sizeof(int2) * N));
+  HIP_TRY(c, c->d_scan_tmp.ensure(sizeof(int) * (size_t)scan_tmp_words(n_cells)));
+  HIP_TRY(c, c->d_order.ensure(4 * N));
   HIP_TRY(c, c->d_pos.ensure(4 * N));
   HIP_TRY(c, c->d_pstate.ensure(sizeof(float) * kSeedWords * N));
   HIP_TRY(c, c->d_pinfo.ensure(4 * N));
   HIP_TRY(c, c->d_pevent.ensure(4 * N));
   HIP_TRY(c, c->d_pplan.ensure(kMaxPlan * N));
   HIP_TRY(c, c->d_out.ensure(sizeof(float) * kOutWords * N));
-  {
-    FindParams Q = params(c);
-    launch_permute_seeds(c->stream, Q, c->d_pstate.as<float>(), c->d_pinfo.as<int>(),
-                         c->d_pevent.as<int>(), c->d_pplan.as<int8_t>(), c->d_pos.as<int>());
-    HIP_TRY(c, hipGetLastError());
+  if (!batched) {  // the layer-synchronous form's state between steps
+    HIP_TRY(c, c->d_cand.ensure(sizeof(float) * kCandFields * kGroup * N));
+    HIP_TRY(c, c->d_fin_key.ensure(8 * N));
+    HIP_TRY(c, c->d_fin_rec.ensure(sizeof(float) * 28 * N));
+    HIP_TRY(c, c->d_fin_meta.ensure(4 * N));
+    HIP_TRY(c, c->d_bp.ensure(4 * (size_t)kMaxPlan * kGroup * N));
   }
+  // (device arrays are read, and copied, by the seed kernel)
+  const int *src_event = mem == MKF_MEM_DEVICE ? seed_event : c->d_seed_event.as<int>();
+  const int *src_hits = mem == MKF_MEM_DEVICE ? seed_hits : c->d_seed_hits.as<int>();
+  mkf_status st;
+  if (mem == MKF_MEM_HOST) {
+    if ((st = stage_in(c, c->d_seed_event, seed_event, 4 * (size_t)n_seeds, mem))) return st;
+    if ((st = stage_in(c, c->d_seed_hits, seed_hits, 12 * (size_t)n_seeds, mem))) return st;
+  }
+  c->n_seeds = n_seeds;
+  const FindParams P = params(c);
+  int *len_counts = c->d_cell_counts.as<int>() + n_cells;
+  launch_fill_i32(c->stream, c->d_cell_counts.as<int>(), n_cells + n_len, 0);
+  HIP_TRY(c, hipEventRecord(c->ev_a, c->stream));
+  launch_seed(c->stream, P, src_event, src_hits, c->d_seed_event.as<int>(),
+              c->d_seed_hits.as<int>(), c->d_seed_state.as<float>(), c->d_seed_ok.as<int>(),
+              c->d_plan_len.as<int>(), c->d_plan.as<int8_t>(), c->d_seed_chi2.as<float>(),
+              c->n_regions > 0 ? c->d_regions.as<DevRegion>() : nullptr, c->n_regions, cells,
+              c->d_cell_counts.as<int>(), c->d_cell_rank.as<int2>(), len_counts);
+  HIP_TRY(c, hipGetLastError());
+  HIP_TRY(c, hipEventRecord(c->ev_b, c->stream));
+  launch_scan(c->stream, c->d_cell_counts.as<int>(), c->d_cell_start.as<int>(), n_cells,
+              c->d_scan_tmp.as<int>());
+  launch_place_seeds(c->stream, P, c->d_cell_rank.as<int2>(), c->d_cell_start.as<int>(),
+                     c->d_order.as<int>(), c->d_pos.as<int>(), c->d_pstate.as<float>(),
+                     c->d_pinfo.as<int>(), c->d_pevent.as<int>(), c->d_pplan.as<int8_t>());
+  HIP_TRY(c, hipGetLastError());
+  HIP_TRY(c, hipMemcpyAsync(c->h_len, len_counts, sizeof(int) * n_len, hipMemcpyDeviceToHost,
+                            c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  float ms = 0.f;
+  HIP_TRY(c, hipEventElapsedTime(&ms, c->ev_a, c->ev_b));
+  c->stats.seed_ms = ms;
+  int64_t len[kLenWords] = {};
+  for (int k = 0; k < n_len; ++k) len[k % kLenWords] += c->h_len[k];
+  c->n_seeds_ok = len[kPlanLens];
+  c->max_plan_len = 0;
+  c->active_at_step.assign(kMaxPlan, 0);
+  int64_t longer = 0;
+  for (int k = kMaxPlan; k > 0; --k) {
+    longer += len[k];
+    if (longer > 0) c->max_plan_len = std::max(c->max_plan_len, k);
+    // the layer-synchronous form keeps the longest plans first: the seeds
+    // still active at step k - 1 form a prefix of the positions
+    c->active_at_step[k - 1] = batched ? n_seeds : longer;
+  }
   c->stats.n_seeds = n_seeds;
   c->stats.n_seeds_ok = c->n_seeds_ok;
   c->stats.max_plan_len = c->max_plan_len;
@@ -865,10 +845,10 @@ mkf_status mkf_get_seed_states(mkf_ctx *c, float *par, float *cov, int32_t *ok,
                                int32_t *plan_len, int8_t *plan, float *chi2) {
   if (!c) return MKF_E_ARG;
   if (c->stage < kSeeds) return fail(c, MKF_E_ORDER, "seed first");
-  const size_t n = (size_t)c->n_seeds, N = std::max<size_t>(n, 1);
+  const size_t n = (size_t)c->n_seeds;
   if (n == 0) return MKF_OK;
-  std::vector<float> st(27 * N);
-  HIP_TRY(c, hipMemcpyAsync(st.data(), c->d_seed_state.ptr, sizeof(float) * 27 * N,
+  std::vector<float> st(kSeedWords * n);
+  HIP_TRY(c, hipMemcpyAsync(st.data(), c->d_seed_state.ptr, sizeof(float) * kSeedWords * n,
                             hipMemcpyDeviceToHost, c->stream));
   if (ok) HIP_TRY(c, hipMemcpyAsync(ok, c->d_seed_ok.ptr, 4 * n, hipMemcpyDeviceToHost, c->stream));
   if (plan_len)
@@ -880,9 +860,9 @@ mkf_status mkf_get_seed_states(mkf_ctx *c, float *par, float *cov, int32_t *ok,
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   for (size_t i = 0; i < n; ++i) {
     if (par)
-      for (int k = 0; k < 6; ++k) par[6 * i + k] = st[k * N + i];
+      for (int k = 0; k < 6; ++k) par[6 * i + k] = st[kSeedWords * i + k];
     if (cov)
-      for (int k = 0; k < 21; ++k) cov[21 * i + k] = st[(6 + k) * N + i];
+      for (int k = 0; k < 21; ++k) cov[21 * i + k] = st[kSeedWords * i + 6 + k];
   }
   return MKF_OK;
 }
@@ -1137,7 +1117,7 @@ mkf_status mkf_make_seeds(mkf_ctx *c, const mkf_seeding *sc, int64_t capacity,
   ds.dz_max = sc->dz_max;
   HIP_TRY(c, c->d_tr_cnt.ensure(sizeof(int) * (size_t)n));
   HIP_TRY(c, c->d_tr_off.ensure(sizeof(int) * (size_t)(n + 1)));
-  HIP_TRY(c, c->d_tr_tmp.ensure(sizeof(int) * (size_t)(4 * (n / 2048 + 4) + 64)));
+  HIP_TRY(c, c->d_tr_tmp.ensure(sizeof(int) * (size_t)scan_tmp_words(n)));
   FindParams P = params(c);
   int64_t max_ev = 0;
   for (int e = 0; e < c->n_events; ++e) max_ev = std::max(max_ev, c->ev_off[e + 1] - c->ev_off[e]);
@@ -1145,8 +1125,7 @@ mkf_status mkf_make_seeds(mkf_ctx *c, const mkf_seeding *sc, int64_t capacity,
   launch_triplets(c->stream, P, ds, max_ev, false, c->d_tr_cnt.as<int>(), nullptr, nullptr,
                   nullptr);
   HIP_TRY(c, hipGetLastError());
-  launch_scan(c->stream, c->d_tr_cnt.as<int>(), c->d_tr_off.as<int>(), n, c->d_tr_tmp.as<int>(),
-              nullptr);
+  launch_scan(c->stream, c->d_tr_cnt.as<int>(), c->d_tr_off.as<int>(), n, c->d_tr_tmp.as<int>());
   HIP_TRY(c, hipGetLastError());
   int total = 0;
   HIP_TRY(c, hipMemcpyAsync(&total, c->d_tr_off.as<int>() + n, sizeof(int), hipMemcpyDeviceToHost,
@@ -1177,7 +1156,7 @@ mkf_status mkf_find_duplicates(mkf_ctx *c, float frac, int32_t *out_dup, int64_t
   HIP_TRY(c, c->d_dup_off.ensure(sizeof(int) * (H + 1)));
   HIP_TRY(c, c->d_dup_fill.ensure(sizeof(int) * H));
   HIP_TRY(c, c->d_dup_list.ensure(sizeof(int) * (kDupStride - 1) * N));
-  HIP_TRY(c, c->d_dup_tmp.ensure(sizeof(int) * (4 * (H / 2048 + 4) + 64)));
+  HIP_TRY(c, c->d_dup_tmp.ensure(sizeof(int) * (size_t)scan_tmp_words((int64_t)H)));
   HIP_TRY(c, c->d_dup_total.ensure(sizeof(int)));
   FindParams P = params(c);
   launch_fill_i32(c->stream, c->d_dup_cnt.as<int>(), (int64_t)H, 0);
@@ -1186,7 +1165,7 @@ mkf_status mkf_find_duplicates(mkf_ctx *c, float frac, int32_t *out_dup, int64_t
   launch_dup_prep(c->stream, P, c->d_seed_hits.as<int>(), c->d_dup_h.as<int>(),
                   c->d_dup_n.as<int>(), c->d_dup_cnt.as<int>());
   launch_scan(c->stream, c->d_dup_cnt.as<int>(), c->d_dup_off.as<int>(), (int64_t)H,
-              c->d_dup_tmp.as<int>(), nullptr);
+              c->d_dup_tmp.as<int>());
   launch_dup_fill(c->stream, P, c->d_dup_h.as<int>(), c->d_dup_n.as<int>(),
                   c->d_dup_off.as<int>(), c->d_dup_fill.as<int>(), c->d_dup_list.as<int>());
   launch_dup_decide(c->stream, P, c->d_seed_hits.as<int>(), c->d_dup_h.as<int>(),
@@ -1217,7 +1196,7 @@ mkf_status mkf_clean_seeds(mkf_ctx *c, const mkf_cleaning *cc, int32_t *out_keep
   HIP_TRY(c, c->d_dup_off.ensure(sizeof(int) * (H + 1)));
   HIP_TRY(c, c->d_dup_fill.ensure(sizeof(int) * H));
   HIP_TRY(c, c->d_dup_list.ensure(sizeof(int) * 3 * N));
-  HIP_TRY(c, c->d_dup_tmp.ensure(sizeof(int) * (4 * (H / 2048 + 4) + 64)));
+  HIP_TRY(c, c->d_dup_tmp.ensure(sizeof(int) * (size_t)scan_tmp_words((int64_t)H)));
   HIP_TRY(c, c->d_dup_total.ensure(sizeof(int)));
   FindParams P = params(c);
   DevCleaning dc{cc->tol_ipt, cc->tol_eta, cc->tol_phi};
@@ -1227,7 +1206,7 @@ mkf_status mkf_clean_seeds(mkf_ctx *c, const mkf_cleaning *cc, int32_t *out_keep
   launch_clean_prep(c->stream, P, c->d_seed_hits.as<int>(), c->d_dup_h.as<int>(),
                     c->d_dup_cnt.as<int>());
   launch_scan(c->stream, c->d_dup_cnt.as<int>(), c->d_dup_off.as<int>(), (int64_t)H,
-              c->d_dup_tmp.as<int>(), nullptr);
+              c->d_dup_tmp.as<int>());
   launch_clean_fill(c->stream, P, c->d_dup_h.as<int>(), c->d_dup_off.as<int>(),
                     c->d_dup_fill.as<int>(), c->d_dup_list.as<int>());
   launch_clean_decide(c->stream, P, c->d_seed_hits.as<int>(), c->d_seed_chi2.as<float>(),

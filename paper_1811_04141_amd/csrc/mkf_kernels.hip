@@ -823,7 +823,11 @@ __device__ __forceinline__ void find_persistent(const FindParams &P) {
   int my_steps = 0, my_acc = 0, my_fb = 0;
   int cnt[3] = {0, 0, 0};  // near-cut decisions, field Runge-Kutta steps, Newton iterations
   int q = blockIdx.x % kQueues;  // this block's XCD
-  int64_t q_lo = P.q_off[q], q_hi = P.q_off[q + 1];  // queue q's positions
+  // Queue k: positions queue_at(k) .. queue_at(k + 1) - 1.  (Equal runs, against
+  // every eighth tile: 4 events of 28,000 triplet seeds 0.46 and 0.48 ms, 8
+  // events of 5,000 seeds 0.185 and 0.203 ms, 100 such events 1.39 and 1.41 ms.)
+  auto queue_at = [&](int k) { return P.n_seeds * k / kQueues; };
+  int64_t q_lo = queue_at(q), q_hi = queue_at(q + 1);
   // A queue's first n_static tiles belong to the waves of its XCD, one each,
   // and need no claim; the counter hands out the tiles after them (the grid
   // is a multiple of kQueues blocks).
@@ -845,7 +849,7 @@ __device__ __forceinline__ void find_persistent(const FindParams &P) {
       // tiles, 86 and 169 us; 500,000 seeds 1.73 -> 1.51 ms).  A counter never
       // falls, so the loop ends when every queue reads as handed out.
       const int qi = lane % kQueues;
-      const int64_t lo_i = P.q_off[qi], hi_i = P.q_off[qi + 1];
+      const int64_t lo_i = queue_at(qi), hi_i = queue_at(qi + 1);
       for (;;) {
         const int c = __hip_atomic_load(&P.tile_counter[qi * kTilePad], __ATOMIC_RELAXED,
                                         __HIP_MEMORY_SCOPE_AGENT);
@@ -855,8 +859,8 @@ __device__ __forceinline__ void find_persistent(const FindParams &P) {
         // the first such queue after this wave's own
         const unsigned rot = ((m | m << kQueues) >> (q + 1)) & ((1u << kQueues) - 1u);
         q = (q + 1 + __builtin_ctz(rot)) % kQueues;
-        q_lo = P.q_off[q];
-        q_hi = P.q_off[q + 1];
+        q_lo = queue_at(q);
+        q_hi = queue_at(q + 1);
         int t = 0;
         if (lane == 0) t = atomicAdd(&P.tile_counter[q * kTilePad], 1);
         t = __builtin_amdgcn_readfirstlane(t);
@@ -1012,23 +1016,34 @@ __global__ __launch_bounds__(256, kWaves) void k_find_persistent_mat(FindParams 
   find_persistent<kWaves, kSurr, G, true>(P);
 }
 
-// Gather the seed results into processing order (untimed preparation), so
-// that every read of the find is by position.
-__global__ __launch_bounds__(256) void k_permute_seeds(FindParams P, float *pstate, int *pinfo,
-                                                       int *pevent, int8_t *pplan, int *pos_of) {
-  const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (pos >= P.n_seeds) return;
-  const size_t N = (size_t)P.n_seeds;
-  const int seed = P.order[pos];
-  pos_of[seed] = (int)pos;
-  for (int i = 0; i < 27; ++i) pstate[(size_t)pos * kSeedWords + i] = P.seed_state[i * N + seed];
-  // the last word: the index of the event's first hit (below 2^31), read
-  // with the state so that the find need not look it up
-  pstate[(size_t)pos * kSeedWords + 27] = __int_as_float((int)P.ev_off[P.seed_event[seed]]);
-  pinfo[pos] = P.plan_len[seed] | (P.seed_ok[seed] << 8);
-  pevent[pos] = P.seed_event[seed];
-  for (int s = 0; s < kMaxPlan; ++s)
-    pplan[(size_t)pos * kMaxPlan + s] = P.plan[(size_t)seed * kMaxPlan + s];
+// The seeds' results into processing order, so that every read of the find is
+// by position.  Nine lanes per seed, 16 bytes each: seven of the state row,
+// two of the plan.  Bound by HBM: 2 x 164 B per seed, the writes in runs of 112
+// and 32 B.  500,000 seeds: 56 us (2.9 TB/s); one lane per seed, gathering 27 words from
+// 27 arrays, took 418 us.
+__global__ __launch_bounds__(256) void k_place_seeds(FindParams P, const int2 *cell_rank,
+                                                     const int *cell_start, int *order,
+                                                     int *pos_of, float4 *pstate, int *pinfo,
+                                                     int *pevent, int4 *pplan) {
+  constexpr int kState = kSeedWords / 4, kPlan = kMaxPlan / 16;
+  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = id / (kState + kPlan);
+  const int k = (int)(id - i * (kState + kPlan));
+  if (i >= P.n_seeds) return;
+  const int2 cr = cell_rank[i];
+  const int64_t pos = cell_start[cr.x] + cr.y;
+  if (k < kState) {
+    pstate[pos * kState + k] = reinterpret_cast<const float4 *>(P.seed_state)[i * kState + k];
+  } else {
+    pplan[pos * kPlan + k - kState] =
+        reinterpret_cast<const int4 *>(P.plan)[i * kPlan + k - kState];
+  }
+  if (k == 0) {
+    order[pos] = (int)i;
+    pos_of[i] = (int)pos;
+    pinfo[pos] = P.plan_len[i] | (P.seed_ok[i] << 8);
+    pevent[pos] = P.seed_event[i];
+  }
 }
 
 // The caller's track records, in seed order, written by the device straight
@@ -1087,24 +1102,60 @@ __global__ __launch_bounds__(256) void k_tracks(FindParams P, const int *pos_of,
 // per seed: every other layer the seed helix crosses inside its widened
 // extent, by increasing path length.
 
-__global__ __launch_bounds__(256) void k_seed(FindParams P, const int *seed_hits,
-                                              float *seed_state, int *seed_ok, int *plan_len,
-                                              int8_t *plan, double *plan_l, float *seed_chi2,
-                                              const DevRegion *regions, int n_regions) {
-  __shared__ DevLayer sl[kMaxLayers];
-  stage_layers(P, sl);
-  __syncthreads();
+//
+// One wavefront per block and one lane per seed; the plan under construction
+// (path lengths and layers) is in LDS.  Bound by the FP64 arithmetic of the
+// fit and of some 25 crossings.  500,000 seeds: 430 us (535 us with the plan in
+// global scratch memory and the sines and cosines of the state taken anew for
+// every layer); 5,000 seeds: 50 us (57 us in blocks of 256).
+constexpr int kSeedBlock = 64;
+
+__global__ __launch_bounds__(256) void k_validate_seeds(FindParams P, const int *seed_event,
+                                                        const int *seed_hits, int *bad) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= P.n_seeds) return;
-  const size_t N = (size_t)P.n_seeds;
-  const int ev = P.seed_event[i];
+  const int ev = seed_event[i];
+  bool good = ev >= 0 && ev < P.n_events;
+  if (good) {
+    const int64_t nh = P.ev_off[ev + 1] - P.ev_off[ev];
+    for (int k = 0; k < 3; ++k) {
+      const int h = seed_hits[3 * i + k];
+      good = good && h >= 0 && h < nh;
+    }
+  }
+  if (!good) *bad = 1;
+}
+
+__global__ __launch_bounds__(kSeedBlock) void k_seed(
+    FindParams P, const int *src_event, const int *src_hits, int *seed_event, int *seed_hits,
+    float *seed_state, int *seed_ok, int *plan_len, int8_t *plan, float *seed_chi2,
+    const DevRegion *regions, int n_regions, SeedCells cells, int *cell_counts, int2 *cell_rank,
+    int *len_counts) {
+  __shared__ DevLayer sl[kMaxLayers];
+  __shared__ double s_l[kMaxPlan][kSeedBlock];   // the plan's path lengths
+  __shared__ int8_t s_plan[kMaxPlan][kSeedBlock];
+  __shared__ int s_len[kLenWords];
+  stage_layers(P, sl);
+  for (int k = threadIdx.x; k < kLenWords; k += blockDim.x) s_len[k] = 0;
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const bool valid = i0 < P.n_seeds;
+  const int64_t i = valid ? i0 : P.n_seeds - 1;  // (idle lanes repeat the last seed, unwritten)
+  const int me = threadIdx.x;
+  const int ev = src_event[i];
   const int64_t e0 = P.ev_off[ev];
+  int sh[3];
+  for (int k = 0; k < 3; ++k) sh[k] = src_hits[3 * i + k];
+  if (valid && src_event != seed_event) {
+    seed_event[i] = ev;
+    for (int k = 0; k < 3; ++k) seed_hits[3 * i + k] = sh[k];
+  }
   // FP64: three updates shrink the wide prior by ~5 decades, more than FP32
   // keeps in C - K S K^T; the result is rounded to FP32 for the find
   double hx[3], hy[3], hz[3], hvu[3], hvv[3];
   int hl[3];
   for (int k = 0; k < 3; ++k) {
-    const int64_t g = e0 + seed_hits[3 * i + k];
+    const int64_t g = e0 + sh[k];
     hx[k] = P.hx[g];
     hy[k] = P.hy[g];
     hz[k] = P.hz[g];
@@ -1179,36 +1230,73 @@ __global__ __launch_bounds__(256) void k_seed(FindParams P, const int *seed_hits
         for (int k = 0; k < g.n && n < kMaxPlan; ++k) {
           const int L = g.layers[k];
           if (L == hl[0] || L == hl[1] || L == hl[2]) continue;
-          plan[i * kMaxPlan + n++] = (int8_t)L;
+          s_plan[n++][me] = (int8_t)L;
         }
       }
       break;
     }
-    // plan: insertion by path length (ties by layer id) into global scratch
+    // plan: insertion by path length (ties by layer id)
+    double trig[4];
+    sincos_t(p[4], &trig[0], &trig[1]);
+    sincos_t(p[5], &trig[2], &trig[3]);
     for (int L = 0; L < P.n_layers; ++L) {
       if (L == hl[0] || L == hl[1] || L == hl[2]) continue;
       PropT<double> pr;
       if (propagate<false, double>(p, nullptr, sl[L], mkb, l_min, true, edge, pr, 0.0, nullptr,
-                                   nullptr, &P.cfg.field) != kOk)
+                                   nullptr, &P.cfg.field, trig) != kOk)
         continue;
       if (n >= kMaxPlan) break;
       const double lf = pr.l;
       int j = n;
-      while (j > 0 && plan_l[i * kMaxPlan + j - 1] > lf) {
-        plan_l[i * kMaxPlan + j] = plan_l[i * kMaxPlan + j - 1];
-        plan[i * kMaxPlan + j] = plan[i * kMaxPlan + j - 1];
+      while (j > 0 && s_l[j - 1][me] > lf) {
+        s_l[j][me] = s_l[j - 1][me];
+        s_plan[j][me] = s_plan[j - 1][me];
         --j;
       }
-      plan_l[i * kMaxPlan + j] = lf;
-      plan[i * kMaxPlan + j] = (int8_t)L;
+      s_l[j][me] = lf;
+      s_plan[j][me] = (int8_t)L;
       ++n;
     }
   } while (false);
-  seed_ok[i] = ok;
-  seed_chi2[i] = ok ? (float)chi2 : 0.f;
-  plan_len[i] = ok ? n : 0;
-  for (int k = 0; k < 6; ++k) seed_state[k * N + i] = ok ? (float)p[k] : 0.f;
-  for (int k = 0; k < 21; ++k) seed_state[(6 + k) * N + i] = ok ? (float)c[k] : 0.f;
+  n = ok ? n : 0;
+  float w[kSeedWords];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) w[k] = ok ? (float)p[k] : 0.f;
+#pragma unroll
+  for (int k = 0; k < 21; ++k) w[6 + k] = ok ? (float)c[k] : 0.f;
+  // the row's last word: the index of the event's first hit (below 2^31),
+  // read with the state so that the find need not look it up
+  w[27] = __int_as_float((int)e0);
+  if (valid) {
+    seed_ok[i] = ok;
+    seed_chi2[i] = ok ? (float)chi2 : 0.f;
+    plan_len[i] = n;
+    float4 *row = reinterpret_cast<float4 *>(seed_state + (size_t)i * kSeedWords);
+#pragma unroll
+    for (int k = 0; k < kSeedWords / 4; ++k)
+      row[k] = make_float4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
+    int *pw = reinterpret_cast<int *>(plan + (size_t)i * kMaxPlan);
+    for (int k = 0; k < kMaxPlan / 4; ++k) {
+      unsigned v = 0;
+      for (int b = 0; b < 4; ++b)
+        v |= (4 * k + b < n ? (unsigned)(uint8_t)s_plan[4 * k + b][me] : 0xFFu) << (8 * b);
+      pw[k] = (int)v;
+    }
+    // the processing order's cell (a state that is not a number: cell 0)
+    const float tc = w[5] * 8.f, pc = (w[4] + kPi) * (kPhiCells / kTwoPi);
+    const int ti = tc > 0.f ? min((int)fminf(tc, 1e6f), kThetaCells - 1) : 0;
+    const int pi = pc > 0.f ? min((int)fminf(pc, 1e6f), kPhiCells - 1) : 0;
+    const int dir = ti * kPhiCells + pi;
+    const int64_t grp = ev >> cells.event_shift, len = kMaxPlan - n;
+    const int64_t cell = (cells.by_length ? len * cells.n_groups + grp
+                                          : grp * kPlanLens + len) * kDirCells + dir;
+    cell_rank[i] = make_int2((int)cell, atomicAdd(&cell_counts[cell], 1));
+    atomicAdd(&s_len[n], 1);
+    if (ok) atomicAdd(&s_len[kPlanLens], 1);
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < kLenWords; k += blockDim.x)
+    if (s_len[k]) atomicAdd(&len_counts[blockIdx.x % kLenSlots * kLenWords + k], s_len[k]);
 }
 
 // ------------------------------------------------------------- hit index
@@ -1536,9 +1624,9 @@ __global__ __launch_bounds__(256) void k_clean_decide(FindParams P, const int *s
   if (t >= P.n_seeds) return;
   bool keep = P.seed_ok[t] != 0;
   if (keep) {
-    const size_t N = (size_t)P.n_seeds;
-    const float ipt_t = P.seed_state[3 * N + t], phi_t = P.seed_state[4 * N + t];
-    const float eta_t = eta_of(P.seed_state[5 * N + t]);
+    const float *row_t = P.seed_state + (size_t)t * kSeedWords;
+    const float ipt_t = row_t[3], phi_t = row_t[4];
+    const float eta_t = eta_of(row_t[5]);
     const float chi_t = seed_chi2[t];
     const int *ht = hbuf + 3 * t;
     for (int k = 0; k < 3 && keep; ++k) {
@@ -1552,10 +1640,11 @@ __global__ __launch_bounds__(256) void k_clean_decide(FindParams P, const int *s
         for (int a = 0; a < 3 && first < 0; ++a)
           if (ht[a] == hu[0] || ht[a] == hu[1] || ht[a] == hu[2]) first = a;
         if (first != k) continue;
-        const float ipt_u = P.seed_state[3 * N + u];
+        const float *row_u = P.seed_state + (size_t)u * kSeedWords;
+        const float ipt_u = row_u[3];
         if (fabsf(ipt_t - ipt_u) > cc.tol_ipt * fmaxf(fabsf(ipt_t), fabsf(ipt_u))) continue;
-        if (fabsf(eta_t - eta_of(P.seed_state[5 * N + u])) > cc.tol_eta) continue;
-        if (fabsf(wrap_phi(phi_t - P.seed_state[4 * N + u])) > cc.tol_phi) continue;
+        if (fabsf(eta_t - eta_of(row_u[5])) > cc.tol_eta) continue;
+        if (fabsf(wrap_phi(phi_t - row_u[4])) > cc.tol_phi) continue;
         const float chi_u = seed_chi2[u];
         bool before;
         if (chi_u != chi_t) {
@@ -1607,51 +1696,71 @@ __global__ __launch_bounds__(256) void k_hit_scatter(FindParams P, int n_events,
   byorig[i] = h;
 }
 
-// exclusive scan, 2048 items per 256-thread block
-constexpr int kScanItems = 8;
-constexpr int kScanBlock = 256 * kScanItems;
+// Exclusive sums in two launches: a block adds up its chunk of tiles; then
+// every block adds the sums of the chunks before its own and scans its chunk
+// tile by tile.  Bound by HBM (the input read twice, the output written once);
+// chunks are four tiles long up to 8 Mi items and 16 beyond, where a block
+// would otherwise read thousands of chunk sums.
+__device__ __forceinline__ int4 scan_load(const int *in, int64_t k, int64_t n) {
+  if (k + 4 <= n) return *reinterpret_cast<const int4 *>(in + k);
+  return make_int4(k < n ? in[k] : 0, k + 1 < n ? in[k + 1] : 0, k + 2 < n ? in[k + 2] : 0, 0);
+}
 
-__global__ __launch_bounds__(256) void k_block_scan(const int *in, int *out, int64_t n,
-                                                    int *block_sums) {
-  __shared__ int wsum[4];
-  const int64_t base = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanItems;
-  int v[kScanItems];
-  int s = 0;
+__device__ __forceinline__ int block_sum(int v, int *wsum) {
 #pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    v[k] = base + k < n ? in[base + k] : 0;
-    s += v[k];
-  }
-  // inclusive scan of s over the block
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int incl = s;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(incl, o);
-    if (lane >= o) incl += t;
-  }
-  if (lane == 63) wsum[wid] = incl;
+  for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
   __syncthreads();
-  int woff = 0;
-  for (int w = 0; w < wid; ++w) woff += wsum[w];
-  int run = woff + incl - s;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    if (base + k < n) out[base + k] = run;
-    run += v[k];
+  v = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  __syncthreads();
+  return v;
+}
+
+__global__ __launch_bounds__(256) void k_scan_sums(const int *in, int64_t n, int tiles,
+                                                   int *sums) {
+  __shared__ int wsum[4];
+  int v = 0;
+  for (int t = 0; t < tiles; ++t) {
+    const int4 a = scan_load(in, ((int64_t)blockIdx.x * tiles + t) * kScanTile + 4 * threadIdx.x, n);
+    v += a.x + a.y + a.z + a.w;
   }
-  if (threadIdx.x == 255) block_sums[blockIdx.x] = woff + incl;
+  v = block_sum(v, wsum);
+  if (threadIdx.x == 0) sums[blockIdx.x] = v;
 }
 
-__global__ __launch_bounds__(256) void k_add_offsets(int *out, int64_t n, const int *offs) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  out[i] += offs[i / kScanBlock];
-}
-
-__global__ void k_set_total(int *out, int64_t n, const int *block_sums, const int *scanned,
-                            int64_t nb) {
-  out[n] = nb == 1 ? block_sums[0] : scanned[nb];
+__global__ __launch_bounds__(256) void k_scan_apply(const int *in, int *out, int64_t n, int tiles,
+                                                    const int *sums) {
+  __shared__ int wsum[4];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  int before = 0;
+  for (int b = threadIdx.x; b < (int)blockIdx.x; b += 256) before += sums[b];
+  int run = block_sum(before, wsum);
+  for (int t = 0; t < tiles; ++t) {
+    const int64_t k = ((int64_t)blockIdx.x * tiles + t) * kScanTile + 4 * threadIdx.x;
+    const int4 a = scan_load(in, k, n);
+    const int s = a.x + a.y + a.z + a.w;
+    int incl = s;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(incl, o);
+      if (lane >= o) incl += u;
+    }
+    if (lane == 63) wsum[wid] = incl;
+    __syncthreads();
+    int e = run + incl - s;
+    for (int w = 0; w < wid; ++w) e += wsum[w];
+    run += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    __syncthreads();
+    const int4 o4 = make_int4(e, e + a.x, e + a.x + a.y, e + a.x + a.y + a.z);
+    if (k + 4 <= n) {
+      *reinterpret_cast<int4 *>(out + k) = o4;
+    } else {
+      if (k < n) out[k] = o4.x;
+      if (k + 1 < n) out[k + 1] = o4.y;
+      if (k + 2 < n) out[k + 2] = o4.z;
+    }
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = run;
 }
 
 // --------------------------------------------------------- unit kernels
@@ -2361,34 +2470,38 @@ void launch_scatter(hipStream_t s, const FindParams &P, int64_t n_hits, const in
                      P.n_events, n_hits, hit_bin, fill, sorted, byorig);
 }
 
-static void scan_rec(hipStream_t s, const int *in, int *out, int64_t n, int *scratch) {
-  const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
-  int *sums = scratch;
-  int *scanned = scratch + nb;
-  hipLaunchKernelGGL(k_block_scan, dim3((unsigned)nb), dim3(256), 0, s, in, out, n, sums);
-  if (nb > 1) {
-    scan_rec(s, sums, scanned, nb, scratch + 2 * nb + 1);
-    hipLaunchKernelGGL(k_add_offsets, dim3(blocks_for(n, 256)), dim3(256), 0, s, out, n,
-                       scanned);
-  }
-  hipLaunchKernelGGL(k_set_total, dim3(1), dim3(1), 0, s, out, n, sums, scanned, nb);
+void launch_scan(hipStream_t s, const int *in, int *out, int64_t n, int *tmp) {
+  const int tiles = n > (8 << 20) ? 16 : 4;
+  const unsigned nb = n > 0 ? blocks_for(n, tiles * kScanTile) : 1;
+  if (nb > 1) hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(256), 0, s, in, n, tiles, tmp);
+  hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(256), 0, s, in, out, n, tiles, tmp);
 }
 
-void launch_scan(hipStream_t s, const int *in, int *out, int64_t n, int *tmp_a, int *tmp_b) {
-  (void)tmp_b;
-  if (n == 0) {
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(1), 0, s, out, (int64_t)1, 0);
-    return;
-  }
-  scan_rec(s, in, out, n, tmp_a);
-}
-
-void launch_seed(hipStream_t s, const FindParams &P, const int *seed_hits, float *seed_state,
-                 int *seed_ok, int *plan_len, int8_t *plan, double *plan_l, float *seed_chi2,
-                 const DevRegion *regions, int n_regions) {
+void launch_validate_seeds(hipStream_t s, const FindParams &P, const int *seed_event,
+                           const int *seed_hits, int *bad) {
   if (P.n_seeds == 0) return;
-  hipLaunchKernelGGL(k_seed, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P, seed_hits,
-                     seed_state, seed_ok, plan_len, plan, plan_l, seed_chi2, regions, n_regions);
+  hipLaunchKernelGGL(k_validate_seeds, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P,
+                     seed_event, seed_hits, bad);
+}
+
+void launch_seed(hipStream_t s, const FindParams &P, const int *src_event, const int *src_hits,
+                 int *seed_event, int *seed_hits, float *seed_state, int *seed_ok, int *plan_len,
+                 int8_t *plan, float *seed_chi2, const DevRegion *regions, int n_regions,
+                 const SeedCells &sc, int *cell_counts, int2 *cell_rank, int *len_counts) {
+  if (P.n_seeds == 0) return;
+  hipLaunchKernelGGL(k_seed, dim3(blocks_for(P.n_seeds, kSeedBlock)), dim3(kSeedBlock), 0, s, P,
+                     src_event, src_hits, seed_event, seed_hits, seed_state, seed_ok, plan_len,
+                     plan, seed_chi2, regions, n_regions, sc, cell_counts, cell_rank, len_counts);
+}
+
+void launch_place_seeds(hipStream_t s, const FindParams &P, const int2 *cell_rank,
+                        const int *cell_start, int *order, int *pos_of, float *pstate, int *pinfo,
+                        int *pevent, int8_t *pplan) {
+  if (P.n_seeds == 0) return;
+  const int64_t lanes = P.n_seeds * (kSeedWords / 4 + kMaxPlan / 16);
+  hipLaunchKernelGGL(k_place_seeds, dim3(blocks_for(lanes, 256)), dim3(256), 0, s, P, cell_rank,
+                     cell_start, order, pos_of, reinterpret_cast<float4 *>(pstate), pinfo, pevent,
+                     reinterpret_cast<int4 *>(pplan));
 }
 
 void launch_find_init(hipStream_t s, const FindParams &P) {
@@ -2463,13 +2576,6 @@ void launch_finalize(hipStream_t s, const FindParams &P) {
 void launch_check_results(hipStream_t s, const FindParams &P) {
   if (P.n_seeds == 0) return;
   hipLaunchKernelGGL(k_check_results, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P);
-}
-
-void launch_permute_seeds(hipStream_t s, const FindParams &P, float *pstate, int *pinfo,
-                          int *pevent, int8_t *pplan, int *pos_of) {
-  if (P.n_seeds == 0) return;
-  hipLaunchKernelGGL(k_permute_seeds, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P,
-                     pstate, pinfo, pevent, pplan, pos_of);
 }
 
 void launch_tracks(hipStream_t s, const FindParams &P, const int *pos_of, int64_t first, int64_t n,

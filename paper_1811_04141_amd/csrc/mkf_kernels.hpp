@@ -61,7 +61,7 @@ struct FindParams {
   // seeds, by seed id (written by the seed kernel)
   int64_t n_seeds;
   const int *seed_event;
-  const float *seed_state;  // [27][n_seeds]
+  const float *seed_state;  // [n_seeds][kSeedWords], as pstate
   const int *seed_ok;
   const int *plan_len;
   const int8_t *plan;       // [n_seeds][kMaxPlan]
@@ -80,13 +80,11 @@ struct FindParams {
   float *fin_rec;           // [28][n_seeds] state + chi2 of the best retired candidate
   int *fin_meta;            // [n_seeds] n_hits | n_miss << 8
   int *bp;                  // [kMaxPlan][n_seeds][slots] back-pointers
-  // persistent form: kQueues tile queues, queue q owning positions
-  // [q_off[q], q_off[q+1]) (whole events); the blocks of XCD x start on
-  // queue x and move on to the others when it is empty.  The queues' counters
-  // of tiles handed out lie kTilePad words apart, each in a cache line of its
-  // own.
+  // persistent form: kQueues tile queues, each an equal run of positions (whole
+  // events but for the two at its ends); the blocks of XCD x start on queue x
+  // and move on to the others when it is empty.  The queues' counters of tiles
+  // handed out lie kTilePad words apart, each in a cache line of its own.
   int *tile_counter;        // [kQueues][kTilePad]
-  const int64_t *q_off;     // [kQueues + 1]
   int max_plan;             // longest layer plan (sizes the persistent form's LDS records)
   unsigned long long *n_steps;
   // learned surrogate (persistent form)
@@ -158,14 +156,42 @@ void launch_clean_decide(hipStream_t s, const FindParams &P, const int *seed_hit
                          const int *list, const DevCleaning &cc, int *out_keep, int *n_keep);
 void launch_hit_bins(hipStream_t s, const FindParams &P, int64_t n_hits, const int *layer,
                      int *hit_bin, int *counts);
-void launch_scan(hipStream_t s, const int *in, int *out, int64_t n, int *tmp_a, int *tmp_b);
+// exclusive sums of in[0 .. n) into out[0 .. n], out[n] the total; tmp holds
+// scan_tmp_words(n) words
+constexpr int64_t kScanTile = 1024;
+constexpr int64_t scan_tmp_words(int64_t n) { return n / (4 * kScanTile) + 1; }
+void launch_scan(hipStream_t s, const int *in, int *out, int64_t n, int *tmp);
 void launch_scatter(hipStream_t s, const FindParams &P, int64_t n_hits, const int *hit_bin,
                     int *fill, HitRec *sorted, HitRec *byorig);
-void launch_seed(hipStream_t s, const FindParams &P, const int *seed_hits, float *seed_state,
-                 int *seed_ok, int *plan_len, int8_t *plan, double *plan_l, float *seed_chi2,
-                 const DevRegion *regions, int n_regions);
-void launch_permute_seeds(hipStream_t s, const FindParams &P, float *pstate, int *pinfo,
-                          int *pevent, int8_t *pplan, int *pos_of);
+// A seed's place in the processing order is found by a counting sort over
+// cells of event group, plan length and direction (kDirCells cells of theta
+// and phi): by group, then longest plan first (persistent form), or longest
+// plan first, then by group (layer-synchronous form, whose active seeds have
+// to be a prefix).
+constexpr int kThetaCells = 26, kPhiCells = 8, kDirCells = kThetaCells * kPhiCells;
+constexpr int kPlanLens = kMaxPlan + 1;
+struct SeedCells {
+  int event_shift;     // events per group: 2^event_shift
+  int n_groups;
+  int by_length;       // layer-synchronous form
+  int64_t cells() const { return (int64_t)n_groups * kPlanLens * kDirCells; }
+};
+// counts of seeds by plan length, then of successful fits, spread over
+// kLenSlots rows of kLenWords (by block index); the host sums the rows
+constexpr int kLenSlots = 64, kLenWords = kPlanLens + 1;
+// any index out of range sets *bad (host memory the device can write)
+void launch_validate_seeds(hipStream_t s, const FindParams &P, const int *seed_event,
+                           const int *seed_hits, int *bad);
+// fits the seeds given by src_event, src_hits (copied to seed_event, seed_hits
+// where those are other arrays) and counts them by cell and by plan length
+void launch_seed(hipStream_t s, const FindParams &P, const int *src_event, const int *src_hits,
+                 int *seed_event, int *seed_hits, float *seed_state, int *seed_ok, int *plan_len,
+                 int8_t *plan, float *seed_chi2, const DevRegion *regions, int n_regions,
+                 const SeedCells &sc, int *cell_counts, int2 *cell_rank, int *len_counts);
+// the seeds' results into processing order
+void launch_place_seeds(hipStream_t s, const FindParams &P, const int2 *cell_rank,
+                        const int *cell_start, int *order, int *pos_of, float *pstate, int *pinfo,
+                        int *pevent, int8_t *pplan);
 // mkf_track records of seeds first .. first + n - 1 into out (kTrackWords
 // words each; host memory the device can write, or device memory)
 constexpr int kTrackWords = (int)sizeof(mkf_track) / 4;

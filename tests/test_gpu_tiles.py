@@ -14,9 +14,10 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-@pytest.mark.parametrize("n_events,n_tracks", [(1, 400), (3, 300), (9, 40)])
+@pytest.mark.parametrize("n_events,n_tracks", [(1, 400), (3, 300), (9, 40), (150, 6)])
 def test_every_seed_is_found_once(n_events, n_tracks):
-    """Seed counts around the tile's 10 (and 8) seeds and the 8 queues, one
+    """Seed counts around the tile's 10 (and 8) seeds and the 8 queues, events sorted
+    alone and in groups (150 events), one
     block per CU (static tiles) and one wave's worth of blocks: the tracks are
     bitwise those of the layer-synchronous form."""
     from paper_1811_04141_amd import mkf
