@@ -328,8 +328,94 @@ __device__ __forceinline__ float hit_chi2(const float *p, const Frame &f, int ki
 // take either way (the band of the parity checks: 1e-3 relative + 1e-2).
 __device__ __forceinline__ float near_cut_band(float cut) { return fmaf(1e-3f, cut, 1e-2f); }
 
-// One lane's window scan: every hit of the window's bins, four at a time.
-// n_near counts the hits whose chi2 lies within near_cut_band of the cut.
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// A window of more than kWideBins bins or kWideRows rows (a candidate whose
+// state is poorly measured: its window may span the whole layer) is scanned by
+// the wavefront's lanes together; alone its lane would hold up the other 63 for
+// hundreds of hits.  Below the line a lane is done in one or two passes of four
+// hits, about what the hand-over costs; lines at 24 bins and 3 rows and at 128
+// and 8 measured within 1.5% of this one.
+constexpr int kWideBins = 48, kWideRows = 5;
+
+// The scan of lane o's window by every lane that is here: the lanes look up
+// one run of bins each, then score the runs' hits one per lane; compatible hits
+// go to lane o's list.  Lane o's values are read into scalar registers, so
+// that this costs the kernels no more than two vector registers.  Bound, like
+// the lane's own scan, by the latency of the run bounds and of the hits, here
+// paid once per 64 of them.  Find kernel without and with it: 2 events x 5,000
+// seeds 0.250 and 0.104 ms, 4 events x 28,000 triplet seeds 0.565 and 0.456 ms,
+// 100 events x 5,000 seeds 1.56 and 1.40 ms (3 waves per SIMD); without it
+// single tiles of 10 seeds took up to 500 us and the launch ended on them.
+template <int N>
+__device__ __forceinline__ void scan_wide(const FindParams &P, const DevLayer &L, int o,
+                                          const Prop &pr, const Frame &f, float chi2_base, int nh,
+                                          int slot, int base, int qlo, int qhi,
+                                          const int (&seg)[4], u64 (&lst)[N], int &n_ext,
+                                          int &n_near) {
+  const float cut = P.cfg.chi2_cut;
+  const float band = near_cut_band(cut);
+  const float4 *hits = reinterpret_cast<const float4 *>(P.sorted);
+  const unsigned long long here = __ballot(true);
+  const int lane = threadIdx.x & 63, n_here = __popcll(here);
+  const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(here >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((unsigned)here, 0u));
+  const float op[3] = {lane_value(pr.p[0], o), lane_value(pr.p[1], o), lane_value(pr.p[2], o)};
+  const Frame of{lane_value(f.tx, o),  lane_value(f.ty, o),  lane_value(f.rx, o),
+                 lane_value(f.ry, o),  lane_value(f.suu, o), lane_value(f.suv, o),
+                 lane_value(f.svv, o)};
+  const int okind = __builtin_amdgcn_readlane(L.kind, o);
+  const int onh = __builtin_amdgcn_readlane(nh, o);
+  const int oslot = __builtin_amdgcn_readlane(slot, o);
+  const float ochi2 = lane_value(chi2_base, o);
+  const int onphi = __builtin_amdgcn_readlane(L.nphi, o);
+  const int oqlo = __builtin_amdgcn_readlane(qlo, o);
+  const int orow = __builtin_amdgcn_readlane(base, o) + oqlo * onphi;
+  const int rows = __builtin_amdgcn_readlane(qhi, o) - oqlo + 1;
+  const int s0 = __builtin_amdgcn_readlane(seg[0], o), s1 = __builtin_amdgcn_readlane(seg[1], o);
+  const int s2 = __builtin_amdgcn_readlane(seg[2], o), s3 = __builtin_amdgcn_readlane(seg[3], o);
+  const int runs = s2 <= s3 ? 2 * rows : rows;  // the second azimuth segments after the first
+  for (int r0 = 0; r0 < runs; r0 += n_here) {
+    int h0 = 0, h1 = 0;
+    if (r0 + rank < runs) {
+      const bool second = r0 + rank >= rows;
+      const int row = orow + (second ? r0 + rank - rows : r0 + rank) * onphi;
+      h0 = P.bin_start[row + (second ? s2 : s0)];
+      h1 = P.bin_start[row + (second ? s3 : s1) + 1];
+    }
+    for (unsigned long long m = __ballot(h1 > h0); m != 0ull; m &= m - 1) {
+      const int src = __ffsll(m) - 1;
+      const int k1 = __builtin_amdgcn_readlane(h1, src);
+      for (int k0 = __builtin_amdgcn_readlane(h0, src); k0 < k1; k0 += n_here) {
+        const int k = k0 + rank;
+        float c2 = -1.f;
+        unsigned order = 0;
+        if (k < k1) {
+          const float4 a = hits[2 * (size_t)k], b = hits[2 * (size_t)k + 1];
+          c2 = hit_chi2(op, of, okind, a, b);
+          order = (unsigned)__float_as_int(b.y);
+          n_near += fabsf(c2 - cut) <= band ? 1 : 0;
+        }
+        for (unsigned long long pm = __ballot(c2 >= 0.f && c2 < cut); pm != 0ull; pm &= pm - 1) {
+          const int from = __ffsll(pm) - 1;
+          const float pc2 = lane_value(c2, from);
+          const unsigned po = (unsigned)__builtin_amdgcn_readlane((int)order, from);
+          if (lane == o) {
+            insert_sorted(lst, ext_key(onh + 1, ochi2 + pc2, oslot, po));
+            ++n_ext;
+          }
+        }
+      }
+    }
+  }
+}
+
+// The window scan of the lanes that are here: every hit of a lane's window, by
+// the lane itself, four at a time, or by all of them (scan_wide).  n_near counts
+// the hits whose chi2 lies within near_cut_band of the cut, in the lane that
+// scored them.
 template <int N>
 __device__ __forceinline__ void scan_window(const FindParams &P, const DevLayer &L, int ev,
                                             const Prop &pr, const Frame &f, float chi2_base,
@@ -339,6 +425,16 @@ __device__ __forceinline__ void scan_window(const FindParams &P, const DevLayer 
   const float band = near_cut_band(cut);
   int base, qlo, qhi, seg[4];
   window_bins(P, L, ev, pr, f, base, qlo, qhi, seg);
+  const int rows = qhi - qlo + 1;
+  const int width = seg[1] - seg[0] + 1 + max(seg[3] - seg[2] + 1, 0);
+  const bool wide = rows > kWideRows || rows * width > kWideBins;
+  unsigned long long wides = __ballot(wide);
+  if (wides != 0ull) {
+    for (; wides != 0ull; wides &= wides - 1)
+      scan_wide(P, L, __ffsll(wides) - 1, pr, f, chi2_base, nh, slot, base, qlo, qhi, seg, lst,
+                n_ext, n_near);
+    if (wide) qhi = qlo - 1;
+  }
   for (int qb = qlo; qb <= qhi; ++qb) {
     const int row = base + qb * L.nphi;
 #pragma unroll
