@@ -131,7 +131,8 @@ struct mkf_ctx {
   DevBuf d_order, d_pos, d_pstate, d_pinfo, d_pevent, d_pplan;
   DevBuf d_bf_tmp;  // backward fit: state between its FP64 and FP32 parts
   DevBuf d_sm_wk, d_sm_n;  // smoothing: forward-pass states per surface, surface counts
-  DevBuf d_tr_cnt, d_tr_off, d_tr_tmp;  // triplet seeding: counts, offsets, scan scratch
+  // triplet seeding: counts (with cursors), offsets, scan scratch, kept triplets
+  DevBuf d_tr_cnt, d_tr_off, d_tr_tmp, d_tr_kept, d_tr_at;
   DevBuf d_dup_h, d_dup_n, d_dup_cnt, d_dup_off, d_dup_fill, d_dup_list, d_dup_tmp, d_dup_total;
   std::vector<int64_t> active_at_step;  // seeds (in processing order) with plan_len > step
   int max_plan_len = 0;
@@ -148,7 +149,7 @@ struct mkf_ctx {
   // pinned host words the find's step count and counters are read back
   // into: [0] steps, then kCounters x kCounterSlots
   unsigned long long *h_cnt = nullptr;
-  int *h_len = nullptr;  // pinned: the seeds' counts by plan length
+  int *h_len = nullptr;  // pinned: the seeds' counts by plan length; other counts read back
   int *h_bad = nullptr;  // pinned: set by the device where an input is out of range
   // pinned slots that the track records pass through on their way to the
   // caller (mkf_get_tracks), and an event for each
@@ -174,7 +175,7 @@ struct mkf_ctx {
                      &d_pevent, &d_pplan, &d_cand, &d_fin_key, &d_fin_rec, &d_fin_meta,
                      &d_bp, &d_out, &d_mlp_param, &d_mlp_m, &d_mlp_v, &d_W1p,
                      &d_W2p, &d_W3p, &d_W2T, &d_W3T, &d_mb1, &d_mb2, &d_mb3, &d_cnt, &d_radii,
-                     &d_tx, &d_tt, &d_tvalid, &d_partial, &d_partial2, &d_loss, &d_grad, &d_bf_tmp, &d_sm_wk, &d_sm_n, &d_tr_cnt, &d_tr_off, &d_tr_tmp, &d_dup_h, &d_dup_n, &d_dup_cnt, &d_dup_off,
+                     &d_tx, &d_tt, &d_tvalid, &d_partial, &d_partial2, &d_loss, &d_grad, &d_bf_tmp, &d_sm_wk, &d_sm_n, &d_tr_cnt, &d_tr_off, &d_tr_tmp, &d_tr_kept, &d_tr_at, &d_dup_h, &d_dup_n, &d_dup_cnt, &d_dup_off,
                      &d_dup_fill, &d_dup_list, &d_dup_tmp, &d_dup_total, &d_seed_chi2};
     for (DevBuf *b : all) b->release();
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
@@ -1115,28 +1116,38 @@ mkf_status mkf_make_seeds(mkf_ctx *c, const mkf_seeding *sc, int64_t capacity,
   ds.d0_max = sc->d0_max;
   ds.z0_max = sc->z0_max;
   ds.dz_max = sc->dz_max;
-  HIP_TRY(c, c->d_tr_cnt.ensure(sizeof(int) * (size_t)n));
+  // triplets that may pass are kept in as many places as there are hits (16 B
+  // each); where a hit's do not fit, they are found again when they are written
+  const int64_t room = n / kTripletSegs;
+  const int64_t n_cursor = kTripletSegs * kTilePad + 1;
+  HIP_TRY(c, c->d_tr_cnt.ensure(sizeof(int) * (size_t)(n + n_cursor)));
   HIP_TRY(c, c->d_tr_off.ensure(sizeof(int) * (size_t)(n + 1)));
   HIP_TRY(c, c->d_tr_tmp.ensure(sizeof(int) * (size_t)scan_tmp_words(n)));
+  HIP_TRY(c, c->d_tr_kept.ensure(sizeof(int4) * (size_t)(room * kTripletSegs)));
+  HIP_TRY(c, c->d_tr_at.ensure(sizeof(int2) * (size_t)n));
+  int *cnt = c->d_tr_cnt.as<int>();
+  const TripletStore st{c->d_tr_kept.as<int4>(), (int)room, cnt + n, cnt + n + n_cursor - 1,
+                        c->d_tr_at.as<int2>()};
   FindParams P = params(c);
   int64_t max_ev = 0;
   for (int e = 0; e < c->n_events; ++e) max_ev = std::max(max_ev, c->ev_off[e + 1] - c->ev_off[e]);
-  launch_fill_i32(c->stream, c->d_tr_cnt.as<int>(), n, 0);
-  launch_triplets(c->stream, P, ds, max_ev, false, c->d_tr_cnt.as<int>(), nullptr, nullptr,
-                  nullptr);
+  launch_fill_i32(c->stream, cnt, n + n_cursor, 0);
+  launch_triplets(c->stream, P, ds, max_ev, cnt, st);
   HIP_TRY(c, hipGetLastError());
-  launch_scan(c->stream, c->d_tr_cnt.as<int>(), c->d_tr_off.as<int>(), n, c->d_tr_tmp.as<int>());
+  launch_scan(c->stream, cnt, c->d_tr_off.as<int>(), n, c->d_tr_tmp.as<int>());
   HIP_TRY(c, hipGetLastError());
-  int total = 0;
-  HIP_TRY(c, hipMemcpyAsync(&total, c->d_tr_off.as<int>() + n, sizeof(int), hipMemcpyDeviceToHost,
+  HIP_TRY(c, hipMemcpyAsync(c->h_len, c->d_tr_off.as<int>() + n, sizeof(int),
+                            hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(c->h_len + 1, st.n_again, sizeof(int), hipMemcpyDeviceToHost,
                             c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  const int total = c->h_len[0];
   if (total < 0) return fail(c, MKF_E_CAPACITY, "more than 2^31 triplets");
   *n_total = total;
   if (total > capacity)
     return fail(c, MKF_E_CAPACITY, "%d triplets, capacity %lld", total, (long long)capacity);
-  launch_triplets(c->stream, P, ds, max_ev, true, c->d_tr_cnt.as<int>(), c->d_tr_off.as<int>(),
-                  out_event, out_hits);
+  launch_triplets_write(c->stream, P, ds, max_ev, cnt, c->d_tr_off.as<int>(), st,
+                        c->h_len[1] > 0, out_event, out_hits);
   HIP_TRY(c, hipGetLastError());
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return MKF_OK;

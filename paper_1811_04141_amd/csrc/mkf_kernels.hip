@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include <algorithm>
+
 #include "mkf_kernels.hpp"
 
 namespace mkf {
@@ -1426,11 +1428,19 @@ __device__ __forceinline__ int bin_of(const DevLayer &L, float x, float y, float
 // has |z| <= z0_max at the point of closest approach to the beam line, which
 // precedes a within half a turn.  The cuts are evaluated in FP64.
 //
-// One thread per hit of the first layer walks the second layer's hits in an
-// azimuth window (every z bin), drops pairs whose straight-line z at the beam
-// line is far outside z0_max, and walks the third layer's hits in an azimuth
-// and z window around the pair's extrapolation.  The windows only bound the
-// search (their margins cover curvature, d0 and dz); the cuts decide.
+// One wavefront per hit a of the first layer.  Its lanes take the second
+// layer's hits b of an azimuth window (every z bin), drop the pairs whose
+// straight-line z at the beam line is far outside z0_max, and gather the others;
+// then each lane takes one pair and walks the third layer's hits c in an azimuth
+// and z window around its extrapolation.  The windows only bound the search
+// (their margins cover curvature, d0 and dz); the cuts decide.  Nearly all c
+// fail the d0 or the dz cut, so both are first bounded from above in FP32
+// (triplet_may_pass), and the lanes evaluate the few triplets left together.
+//
+// Bound by instruction issue in the walk over c (some 9 million candidates per
+// event of 5,000 tracks).  20 events x 5,000 tracks: 2.04 ms for the whole call,
+// against 51 ms with one lane per hit a and the FP64 cuts on every c, in two
+// passes.
 
 // exact cuts of one triplet (FP64)
 __device__ __forceinline__ bool triplet_passes(const DevCfg &cfg, const DevSeeding &sc, double ax,
@@ -1467,34 +1477,93 @@ __device__ __forceinline__ bool triplet_passes(const DevCfg &cfg, const DevSeedi
   return fabs(z0) <= (double)sc.z0_max;
 }
 
-// the bin rows [qlo, qhi] x azimuth window [phi - dphi, phi + dphi] of one
-// layer (two azimuth segments where it wraps); fn(hit record) per hit
-template <class Fn>
-__device__ __forceinline__ void walk_window(const FindParams &P, const DevLayer &L, int ev, float phi,
-                                            float dphi, int qlo, int qhi, Fn fn) {
-  const int nphi = L.nphi;
-  int s0lo = 0, s0hi = nphi - 1, s1lo = 1, s1hi = 0;
+// False only where the triplet cannot pass: its d0 or its dz is beyond the cut by
+// more than FP32 can be wrong about them.  With u = b - a, v = c - a, w = c - b,
+// cr = u x v and W = (v_y u^2 - u_y v^2, u_x v^2 - v_x u^2), the circle's centre
+// is a + W / (2 cr), its radius rho = |W| / (2 |cr|) with |W| = |u| |v| |w|, and
+//   d0 = |centre| - rho = (a^2 cr + a . W) / (|cr| (|centre| + rho)),
+// a form without cancellation for straight tracks.  Every term on the left is
+// a sum of products of differences of the coordinates, each rounded a few times:
+// the error of a^2 cr + a . W and of d0_max cr centre is below 12 roundings
+// (7e-7) of (|a| + d0_max) (|a| |u| |v| + |u| |v| (|u| + |v|)), taken here as 4e-6
+// of a bound on that.  A chord turns by 2 asin(|u| / 2 rho), so the arcs that dz
+// takes are s_ab / s_ac = asin(|u| k) / asin(|v| k), k = 1 / (2 rho), with asin(x) / x
+// summed to x^6 (within 2e-5 for x <= 0.4; beyond, the triplet is let through), as
+// is one straight enough (|cr| < 1e-5 (u^2 + v^2)) for FP64 to round d0 visibly.
+__device__ __forceinline__ bool triplet_may_pass(const DevSeeding &sc, float ax, float ay,
+                                                 float az, float ra, float ux, float uy, float u2,
+                                                 float bx, float by, float uz, float cx, float cy,
+                                                 float cz) {
+  const float vx = cx - ax, vy = cy - ay, wx = cx - bx, wy = cy - by;
+  const float v2 = fmaf(vx, vx, vy * vy), w2 = fmaf(wx, wx, wy * wy);
+  const float cr = fmaf(ux, vy, -uy * vx);
+  const float Wx = fmaf(vy, u2, -uy * v2), Wy = fmaf(ux, v2, -vx * u2);
+  const float m = u2 + v2;
+  const float lhs = fmaf(ra * ra, cr, fmaf(ax, Wx, ay * Wy));
+  const float ox = fmaf(cr, ax, 0.5f * Wx), oy = fmaf(cr, ay, 0.5f * Wy);
+  const float W = __builtin_amdgcn_sqrtf(u2 * v2 * w2);
+  const float rhs = sc.d0_max * (0.5f * W + __builtin_amdgcn_sqrtf(fmaf(ox, ox, oy * oy)));
+  const float err = 4e-6f * m * (ra + sc.d0_max) *
+                    fmaf(0.75f, __builtin_amdgcn_sqrtf(m), 0.5f * ra);
+  if (fabsf(cr) < 1e-5f * m) return true;
+  if (fabsf(lhs) > fmaf(rhs, 1.0001f, err)) return false;
+  const float k = fabsf(cr) * __builtin_amdgcn_rcpf(W);
+  const float x = u2 * k * k, y = v2 * k * k;  // (|u| k)^2, (|v| k)^2
+  if (!(y < 0.16f)) return true;
+  const float pu = fmaf(x, fmaf(x, fmaf(x, 15.f / 336.f, 3.f / 40.f), 1.f / 6.f), 1.f);
+  const float pv = fmaf(y, fmaf(y, fmaf(y, 15.f / 336.f, 3.f / 40.f), 1.f / 6.f), 1.f);
+  const float ratio = __builtin_amdgcn_sqrtf(u2 * __builtin_amdgcn_rcpf(v2)) * pu *
+                      __builtin_amdgcn_rcpf(pv);
+  const float vz = cz - az;
+  // (a value that is not a number passes)
+  return !(fabsf(fmaf(-vz, ratio, uz)) >
+           fmaf(1e-4f, fabsf(vz) + fabsf(uz) + sc.dz_max, sc.dz_max + 1e-5f));
+}
+
+// The azimuth window [phi - dphi, phi + dphi] of a layer as up to two runs of
+// bins per row, [lo[0], hi[0]] and, where it wraps, [lo[1], hi[1]] (else empty).
+struct PhiRuns {
+  int lo[2], hi[2];
+};
+__device__ __forceinline__ PhiRuns phi_runs(const DevLayer &L, float phi, float dphi) {
+  PhiRuns r{{0, 1}, {L.nphi - 1, 0}};
   if (dphi < kPi) {
     const int blo = (int)floorf((phi - dphi + kPi) * L.phi_scale);
     const int bhi = (int)floorf((phi + dphi + kPi) * L.phi_scale);
-    if (bhi - blo + 1 < nphi) {
+    if (bhi - blo + 1 < L.nphi) {
       if (blo < 0) {
-        s0lo = blo + nphi; s1lo = 0; s1hi = bhi;
-      } else if (bhi >= nphi) {
-        s0lo = blo; s1lo = 0; s1hi = bhi - nphi;
+        r.lo[0] = blo + L.nphi; r.lo[1] = 0; r.hi[1] = bhi;
+      } else if (bhi >= L.nphi) {
+        r.lo[0] = blo; r.lo[1] = 0; r.hi[1] = bhi - L.nphi;
       } else {
-        s0lo = blo; s0hi = bhi;
+        r.lo[0] = blo; r.hi[0] = bhi;
       }
     }
   }
-  const int base = ev * P.bins_per_event + L.bin_base;
+  return r;
+}
+
+// fn(position in the sorted hits, the record's first half) for every hit of
+// rows [qlo, qhi] x runs, the records requested four at a time (the sorted array
+// is padded past its end)
+template <class Fn>
+__device__ __forceinline__ void walk_runs(const FindParams &P, int base, int nphi,
+                                          const PhiRuns &r, int qlo, int qhi, Fn fn) {
+  const float4 *hits = reinterpret_cast<const float4 *>(P.sorted);
   for (int qb = qlo; qb <= qhi; ++qb) {
     const int row = base + qb * nphi;
+#pragma unroll
     for (int sg = 0; sg < 2; ++sg) {
-      const int lo = sg == 0 ? s0lo : s1lo, hi = sg == 0 ? s0hi : s1hi;
-      if (lo > hi) continue;
-      const int h0 = P.bin_start[row + lo], h1 = P.bin_start[row + hi + 1];
-      for (int k = h0; k < h1; ++k) fn(P.sorted[k]);
+      if (r.lo[sg] > r.hi[sg]) continue;
+      const int h0 = P.bin_start[row + r.lo[sg]], h1 = P.bin_start[row + r.hi[sg] + 1];
+      for (int k = h0; k < h1; k += 4) {
+        float4 h[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) h[j] = hits[2 * (size_t)(k + j)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (k + j < h1) fn(k + j, h[j]);
+      }
     }
   }
 }
@@ -1506,55 +1575,264 @@ __device__ __forceinline__ float bend_window(float r0, float r1, float rho_min, 
   return asinf(s1) - asinf(s0) + d0 / r0 + d0 / r1 + 2e-3f;
 }
 
-// One thread per first-layer hit, taken in the hit index's order within
-// its event (blockIdx.y), so that neighbouring lanes walk neighbouring
-// windows; counts and offsets are indexed by that sorted position.
-template <bool kWrite>
-__global__ __launch_bounds__(256) void k_triplets(FindParams P, DevSeeding sc, int *counts,
-                                                  const int *offsets, int *out_event,
-                                                  int *out_hits) {
+__device__ __forceinline__ int wave_inclusive(int v, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(v, o);
+    if (lane >= o) v += u;
+  }
+  return v;
+}
+
+// One wavefront per first-layer hit of event blockIdx.y, in the hit index's
+// order; counts, offsets and kept are indexed by that sorted position.  The
+// triplets of a hit come in the order of b, then of c, in the index.
+//   gather: the triplets that may pass go to the store, up to kTripletList per
+//     hit and while its segment has room; k_triplets_cut takes the cuts, one
+//     lane per triplet, and k_triplets_place puts those that pass in place.
+//     (With the cuts taken here, by the few lanes that hold a triplet, their
+//     FP64 arithmetic was half of the kernel's instructions and left it three
+//     waves per SIMD: 2.80 ms on 20 events x 5,000 tracks, where gathering takes
+//     2.05 at six waves per SIMD (2.30 at four) and the cuts 0.04.)
+//   count, write: the same with the cuts, for the hits that did not fit.
+enum TripletMode { kGather = 0, kCount = 1, kWriteOut = 2 };
+constexpr int kTripletKeep = 4;  // c that a lane notes per walk
+constexpr int kTripletList = 256;
+template <int kMode>
+__global__ __launch_bounds__(256, kMode == kGather ? 6 : 1) void k_triplets(FindParams P, DevSeeding sc, int *counts,
+                                                  const int *offsets, TripletStore st,
+                                                  int *out_event, int *out_hits) {
   __shared__ DevLayer sl[kMaxLayers];
+  __shared__ int s_shift[4][64], s_end[4][64];  // runs of b: sorted position - ordinal, end ordinal
+  __shared__ int s_pair[4][128];                // sorted positions of the gathered b
+  __shared__ int s_c[4][kTripletKeep][64];
+  __shared__ int2 s_list[4][kMode == kGather ? kTripletList : 1];  // the hit's (b, c) so far
+  if (kMode != kGather && *st.n_again == 0) return;
   stage_layers(P, sl);
   __syncthreads();
   const int e = blockIdx.y;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const DevLayer &L0 = sl[sc.layer[0]], &L1 = sl[sc.layer[1]], &L2 = sl[sc.layer[2]];
-  const int first = e * P.bins_per_event + L0.bin_base;
-  const int idx = P.bin_start[first] + blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= P.bin_start[first + L0.nq * L0.nphi]) return;
-  const HitRec ha = P.sorted[idx];
-  const float ax = ha.x, ay = ha.y, az = ha.z;
-  const float ra = sqrtf(fmaf(ax, ax, ay * ay));
+  const int ev0 = e * P.bins_per_event;
+  const int first = P.bin_start[ev0 + L0.bin_base];
+  const int last = P.bin_start[ev0 + L0.bin_base + L0.nq * L0.nphi];
   const float rho_min = sc.pt_min / fabsf(P.cfg.mkb);
   const float R0 = L0.pos, R1 = L1.pos, R2 = L2.pos;
   const float dphi1 = bend_window(R0, R1, rho_min, sc.d0_max);
   const float dphi2 = bend_window(R1, R2, rho_min, sc.d0_max);
-  const int pos = kWrite ? offsets[idx] : 0;
-  int n = 0;
-  walk_window(P, L1, e, atan2f(ay, ax), dphi1, 0, L1.nq - 1, [&](const HitRec &hb) {
-    const float rb = sqrtf(fmaf(hb.x, hb.x, hb.y * hb.y));
-    const float Z = hb.z - az;
-    const float lever = ra / (rb - ra);
-    // straight-line z at the beam line, against z0_max with room for the
-    // arc-versus-radius differences (d0, bending) and dz
-    const float z0e = az - Z * lever;
-    if (fabsf(z0e) > sc.z0_max + 1.f + (0.1f * fabsf(Z) + sc.dz_max) * (lever + 1.f)) return;
-    const float k = (R2 - ra) / (rb - ra);
-    const float zp = az + Z * k;
-    const float hw = (0.1f * fabsf(Z) + 2.f * sc.dz_max) * k + 0.5f;
-    const int qlo = clampi((int)floorf((zp - hw - L2.q_lo) * L2.q_scale), 0, L2.nq - 1);
-    const int qhi = clampi((int)floorf((zp + hw - L2.q_lo) * L2.q_scale), 0, L2.nq - 1);
-    walk_window(P, L2, e, atan2f(hb.y, hb.x), dphi2, qlo, qhi, [&](const HitRec &hc) {
-      if (!triplet_passes(P.cfg, sc, ax, ay, az, hb.x, hb.y, hb.z, hc.x, hc.y, hc.z)) return;
-      if (kWrite) {
-        out_event[pos + n] = e;
-        out_hits[3 * (size_t)(pos + n)] = ha.orig;
-        out_hits[3 * (size_t)(pos + n) + 1] = hb.orig;
-        out_hits[3 * (size_t)(pos + n) + 2] = hc.orig;
+  for (int idx = first + blockIdx.x * 4 + wv; idx < last; idx += gridDim.x * 4) {
+    if (kMode != kGather && st.kept[idx].x >= 0) continue;
+    const HitRec ha = P.sorted[idx];
+    const float ax = ha.x, ay = ha.y, az = ha.z;
+    const float ra = sqrtf(fmaf(ax, ax, ay * ay));
+    int total = 0, n_pair = 0;  // (the same in all lanes)
+    // up to 64 gathered pairs, one per lane
+    auto take_pairs = [&](int n) {
+      const bool on = lane < n;
+      const int kb = s_pair[wv][on ? lane : 0];
+      const HitRec hb = P.sorted[kb];
+      const float rb = sqrtf(fmaf(hb.x, hb.x, hb.y * hb.y));
+      const float Z = hb.z - az;
+      const float ux = hb.x - ax, uy = hb.y - ay, u2 = fmaf(ux, ux, uy * uy);
+      const float k = (R2 - ra) / (rb - ra);
+      const float zp = az + Z * k;
+      const float hw = (0.1f * fabsf(Z) + 2.f * sc.dz_max) * k + 0.5f;
+      const int qlo = clampi((int)floorf((zp - hw - L2.q_lo) * L2.q_scale), 0, L2.nq - 1);
+      const int qhi = clampi((int)floorf((zp + hw - L2.q_lo) * L2.q_scale), 0, L2.nq - 1);
+      const PhiRuns runs = phi_runs(L2, atan2f(hb.y, hb.x), dphi2);
+      const int base = ev0 + L2.bin_base;
+      // Rounds of kTripletKeep noted c per lane, the walk repeated where a lane
+      // has more; when all are counted, the places are known and the triplets
+      // are put there, from the notes if there was one round, else in the same
+      // rounds again.
+      int noted = 0, most = 0, n_c = 0, incl = 0, skip = 0;
+      int64_t pos = 0;
+      bool putting = false;
+      for (;;) {
+        int ord = 0;
+        walk_runs(P, base, L2.nphi, runs, qlo, on ? qhi : qlo - 1, [&](int c, const float4 &h) {
+          if (triplet_may_pass(sc, ax, ay, az, ra, ux, uy, u2, hb.x, hb.y, Z, h.x, h.y, h.z)) {
+            if (ord >= skip && ord < skip + kTripletKeep) s_c[wv][ord - skip][lane] = c;
+            ++ord;
+          }
+        });
+        if (!putting && skip == 0) {
+          noted = ord;
+          while (__ballot(noted > most) != 0ull) most += kTripletKeep;
+        }
+        int pass = 0;  // which of this round's c pass
+#pragma unroll 1
+        for (int t = 0; t < kTripletKeep; ++t) {
+          if (skip + t >= noted) break;
+          if constexpr (kMode == kGather) {
+            pass |= 1 << t;
+            continue;
+          }
+          const HitRec hc = P.sorted[s_c[wv][t][lane]];
+          if (triplet_passes(P.cfg, sc, ax, ay, az, hb.x, hb.y, hb.z, hc.x, hc.y, hc.z))
+            pass |= 1 << t;
+        }
+        skip += kTripletKeep;
+        if (!putting) {
+          n_c += __popc(pass);
+          if (skip < most) continue;
+          incl = wave_inclusive(n_c, lane);
+          pos = (kMode == kWriteOut ? (int64_t)offsets[idx] : 0) + total + incl - n_c;
+          if (kMode == kCount) break;
+          putting = true;
+          skip = 0;
+          if (most > kTripletKeep) continue;
+        }
+#pragma unroll 1
+        for (int t = 0; t < kTripletKeep; ++t)
+          if ((pass >> t) & 1) {
+            const int kc = s_c[wv][t][lane];
+            if constexpr (kMode == kWriteOut) {
+              out_event[pos] = e;
+              out_hits[3 * pos] = ha.orig;
+              out_hits[3 * pos + 1] = hb.orig;
+              out_hits[3 * pos + 2] = P.sorted[kc].orig;
+            } else if (pos < kTripletList) {
+              s_list[wv][pos] = make_int2(kb, kc);
+            }
+            ++pos;
+          }
+        if (skip >= most || most <= kTripletKeep) break;
       }
-      ++n;
-    });
-  });
-  if (!kWrite) counts[idx] = n;
+      total += __shfl(incl, 63);
+    };
+    const PhiRuns runs = phi_runs(L1, atan2f(ay, ax), dphi1);
+    const int segs = runs.lo[1] <= runs.hi[1] ? 2 : 1, n_runs = L1.nq * segs;
+    for (int r0 = 0; r0 < n_runs; r0 += 64) {
+      const int r = r0 + lane;
+      int h0 = 0, len = 0;
+      if (r < n_runs) {
+        const int sg = segs == 2 ? r & 1 : 0;
+        const int row = ev0 + L1.bin_base + (segs == 2 ? r >> 1 : r) * L1.nphi;
+        h0 = P.bin_start[row + (sg ? runs.lo[1] : runs.lo[0])];
+        len = P.bin_start[row + (sg ? runs.hi[1] : runs.hi[0]) + 1] - h0;
+      }
+      const int end = wave_inclusive(len, lane);
+      s_shift[wv][lane] = h0 - (end - len);
+      s_end[wv][lane] = end;
+      const int n_b = __shfl(end, 63);
+      wave_sync();
+      for (int t0 = 0; t0 < n_b; t0 += 64) {
+        const int t = t0 + lane;
+        bool keep = t < n_b;
+        int kb = 0;
+        if (keep) {
+          int lo = 0;  // the first run that ends beyond ordinal t
+#pragma unroll
+          for (int step = 32; step > 0; step >>= 1)
+            if (s_end[wv][lo + step - 1] <= t) lo += step;
+          kb = t + s_shift[wv][lo];
+          const float4 h = reinterpret_cast<const float4 *>(P.sorted)[2 * (size_t)kb];
+          const float rb = sqrtf(fmaf(h.x, h.x, h.y * h.y));
+          const float Z = h.z - az;
+          const float lever = ra / (rb - ra);
+          // straight-line z at the beam line, against z0_max with room for
+          // the arc-versus-radius differences (d0, bending) and dz
+          const float z0e = az - Z * lever;
+          keep = !(fabsf(z0e) > sc.z0_max + 1.f + (0.1f * fabsf(Z) + sc.dz_max) * (lever + 1.f));
+        }
+        const unsigned long long m = __ballot(keep);
+        if (keep) s_pair[wv][n_pair + __popcll(m & ((1ull << lane) - 1ull))] = kb;
+        n_pair += __popcll(m);
+        wave_sync();
+        if (n_pair >= 64) {
+          take_pairs(64);
+          n_pair -= 64;
+          const int rest = s_pair[wv][64 + lane];
+          wave_sync();
+          if (lane < n_pair) s_pair[wv][lane] = rest;
+          wave_sync();
+        }
+      }
+      wave_sync();
+    }
+    if (n_pair > 0) take_pairs(n_pair);
+    wave_sync();
+    if constexpr (kMode == kGather) {
+      int at = -1;
+      if (lane == 0) {
+        const int seg = (blockIdx.x + blockIdx.y * gridDim.x) % kTripletSegs;
+        int *cursor = &st.cursor[seg * kTilePad];
+        // (a full segment's cursor is left alone, so that it cannot wrap)
+        if (total <= kTripletList &&
+            __hip_atomic_load(cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < st.seg_size) {
+          const int a = total > 0 ? atomicAdd(cursor, total) : 0;
+          if (a + total <= st.seg_size) {
+            at = seg * st.seg_size + a;
+          } else {  // the segment's end holds no triplet
+            for (int t = a; t < st.seg_size; ++t) st.triplet[seg * st.seg_size + t].x = -1;
+          }
+        } else if (total == 0) {
+          at = 0;
+        }
+        if (at < 0) atomicAdd(st.n_again, 1);
+        st.kept[idx] = make_int2(at, total);
+      }
+      at = __builtin_amdgcn_readfirstlane(at);
+      if (at >= 0)
+        for (int t = lane; t < total; t += 64) {
+          const int2 bc = s_list[wv][t];
+          st.triplet[at + t] = make_int4(idx, bc.x, bc.y, 0);
+        }
+      wave_sync();  // read before the next hit's triplets overwrite the list
+    } else if constexpr (kMode == kCount) {
+      if (lane == 0) counts[idx] = total;
+    }
+  }
+}
+
+// The cuts of the gathered triplets, one lane each: .w = 1 for those that pass,
+// counted by first hit.  One segment per blockIdx.x.
+__global__ __launch_bounds__(256) void k_triplets_cut(FindParams P, DevSeeding sc, TripletStore st,
+                                                      int *counts) {
+  const int n = min(st.cursor[blockIdx.x * kTilePad], st.seg_size);
+  int4 *triplet = st.triplet + (size_t)blockIdx.x * st.seg_size;
+  const float4 *hits = reinterpret_cast<const float4 *>(P.sorted);
+  for (int i = blockIdx.y * 256 + threadIdx.x; i < n; i += gridDim.y * 256) {
+    const int4 t = triplet[i];
+    if (t.x < 0) continue;
+    const float4 a = hits[2 * (size_t)t.x], b = hits[2 * (size_t)t.y], c = hits[2 * (size_t)t.z];
+    if (triplet_passes(P.cfg, sc, a.x, a.y, a.z, b.x, b.y, b.z, c.x, c.y, c.z)) {
+      triplet[i].w = 1;
+      atomicAdd(&counts[t.x], 1);
+    }
+  }
+}
+
+// The triplets that passed to their places, eight lanes per first-layer hit.
+__global__ __launch_bounds__(256) void k_triplets_place(FindParams P, DevSeeding sc,
+                                                        const int *counts, const int *offsets,
+                                                        TripletStore st, int *out_event,
+                                                        int *out_hits) {
+  const int e = blockIdx.y;
+  const DevLayer &L0 = P.layers[sc.layer[0]];
+  const int first = P.bin_start[e * P.bins_per_event + L0.bin_base];
+  const int last = P.bin_start[e * P.bins_per_event + L0.bin_base + L0.nq * L0.nphi];
+  const int sub = threadIdx.x & 7, group = threadIdx.x & 56;
+  for (int idx = first + (blockIdx.x * 256 + threadIdx.x) / 8; idx < last;
+       idx += gridDim.x * 32) {
+    const int2 kept = st.kept[idx];
+    if (kept.x < 0 || counts[idx] == 0) continue;
+    const int a = P.sorted[idx].orig;
+    int64_t pos = offsets[idx];
+    for (int t0 = 0; t0 < kept.y; t0 += 8) {
+      const int4 t = t0 + sub < kept.y ? st.triplet[kept.x + t0 + sub] : make_int4(0, 0, 0, 0);
+      const unsigned m = (unsigned)(__ballot(t.w != 0) >> group) & 0xFFu;
+      if (t.w) {
+        const int64_t p = pos + __popc(m & ((1u << sub) - 1u));
+        out_event[p] = e;
+        out_hits[3 * p] = a;
+        out_hits[3 * p + 1] = P.sorted[t.y].orig;
+        out_hits[3 * p + 2] = P.sorted[t.z].orig;
+      }
+      pos += __popc(m);
+    }
+  }
 }
 
 // ---------------------------------------------------- duplicate removal
@@ -2718,17 +2996,34 @@ void launch_smooth(hipStream_t s, const FindParams &P, const int *seed_hits, flo
                      n_surf, out_par, out_cov, out_n);
 }
 
+// enough blocks to fill the device some times over, each a few hits long
+constexpr int kTripletBlocks = 16384;
+static dim3 triplet_grid(const FindParams &P, int64_t max_event_hits, int per_block) {
+  const int64_t per_event = std::max<int64_t>(1, kTripletBlocks / P.n_events);
+  return dim3((unsigned)std::min<int64_t>((max_event_hits + per_block - 1) / per_block, per_event),
+              (unsigned)P.n_events);
+}
+
 void launch_triplets(hipStream_t s, const FindParams &P, const DevSeeding &sc,
-                     int64_t max_event_hits, bool write, int *counts, const int *offsets,
-                     int *out_event, int *out_hits) {
+                     int64_t max_event_hits, int *counts, const TripletStore &st) {
   if (max_event_hits == 0 || P.n_events == 0) return;
-  const dim3 grid(blocks_for(max_event_hits, 256), (unsigned)P.n_events);
-  if (write)
-    hipLaunchKernelGGL(k_triplets<true>, grid, dim3(256), 0, s, P, sc, counts, offsets, out_event,
-                       out_hits);
-  else
-    hipLaunchKernelGGL(k_triplets<false>, grid, dim3(256), 0, s, P, sc, counts, offsets,
-                       out_event, out_hits);
+  const dim3 grid = triplet_grid(P, max_event_hits, 4);
+  hipLaunchKernelGGL(k_triplets<kGather>, grid, dim3(256), 0, s, P, sc, counts, nullptr, st,
+                     nullptr, nullptr);
+  hipLaunchKernelGGL(k_triplets_cut, dim3(kTripletSegs, 16), dim3(256), 0, s, P, sc, st, counts);
+  hipLaunchKernelGGL(k_triplets<kCount>, grid, dim3(256), 0, s, P, sc, counts, nullptr, st,
+                     nullptr, nullptr);
+}
+
+void launch_triplets_write(hipStream_t s, const FindParams &P, const DevSeeding &sc,
+                           int64_t max_event_hits, int *counts, const int *offsets,
+                           const TripletStore &st, bool again, int *out_event, int *out_hits) {
+  if (max_event_hits == 0 || P.n_events == 0) return;
+  hipLaunchKernelGGL(k_triplets_place, triplet_grid(P, max_event_hits, 32), dim3(256), 0, s, P, sc,
+                     counts, offsets, st, out_event, out_hits);
+  if (again)
+    hipLaunchKernelGGL(k_triplets<kWriteOut>, triplet_grid(P, max_event_hits, 4), dim3(256), 0, s,
+                       P, sc, counts, offsets, st, out_event, out_hits);
 }
 
 void launch_dup_prep(hipStream_t s, const FindParams &P, const int *seed_hits, int *hbuf, int *hn,

@@ -126,13 +126,27 @@ struct DevSeeding {
   int layer[3];
   float pt_min, d0_max, z0_max, dz_max;
 };
-// counts[i]: triplets whose first hit is the hit at binned position i
-// (counting pass; the other positions are left alone); with offsets, writes
-// them (event, three event-local hit indices).  max_event_hits bounds the
-// hits of one event.
+// triplets that may pass the cuts, in kTripletSegs segments of seg_size places,
+// each with a cursor in a cache line of its own: binned positions of a, b, c (a
+// < 0: none) and whether the cuts passed; kept[i]: where those of the hit at
+// binned position i lie and their number, or x < 0 where they did not fit
+// (n_again counts such hits)
+constexpr int kTripletSegs = 64;
+struct TripletStore {
+  int4 *triplet;
+  int seg_size;
+  int *cursor;   // [kTripletSegs][kTilePad], zero
+  int *n_again;  // zero
+  int2 *kept;
+};
+// counts[i]: triplets whose first hit is the hit at binned position i (the
+// other positions are left alone).  max_event_hits bounds the hits of one event.
 void launch_triplets(hipStream_t s, const FindParams &P, const DevSeeding &sc,
-                     int64_t max_event_hits, bool write, int *counts, const int *offsets,
-                     int *out_event, int *out_hits);
+                     int64_t max_event_hits, int *counts, const TripletStore &st);
+// the triplets (event, three event-local hit indices) to their places
+void launch_triplets_write(hipStream_t s, const FindParams &P, const DevSeeding &sc,
+                           int64_t max_event_hits, int *counts, const int *offsets,
+                           const TripletStore &st, bool again, int *out_event, int *out_hits);
 // duplicate-track removal: per track its sorted hits (hbuf [n_seeds][kDupStride],
 // hn), the tracks on every hit (CSR: cnt, off, fill, list), the decision
 constexpr int kDupStride = 36;
