@@ -3,7 +3,7 @@
 // and activations on the matrix cores, FP32 accumulation and master
 // weights).
 //
-// Training: each wavefront takes 64 samples, runs the forward pass, the
+// Training: each block takes 64 samples, runs the forward pass, the
 // backward pass (dH = W^T dZ on MFMA with transposed weight images) and the
 // weight gradients (dW = dZ H^T on MFMA with samples as the reduction
 // dimension, from unit-major LDS tiles), and writes its partial gradient.
@@ -116,185 +116,207 @@ struct GradParams {
 
 constexpr int kLdU = 72;  // unit-major tiles: [unit][64 samples + 8]
 
-// acc[mt][nt] = A (MT*32 x 64, unit-major LDS) . B^T (NT*32 x 64 unit-major):
-// products summed over the 64 samples of the wave.
-template <int MT, int NT>
-__device__ __forceinline__ void gemm_uu(const __bf16 *A, const __bf16 *B, f32x16 (&acc)[MT][NT]) {
+// A wavefront's 32 x 32 tile of one product, accumulated over KC chunks of 16:
+// a[kc] rows of the left operand, B the right operand's rows (both as the
+// instruction takes them: row r, k = 8h .. 8h + 7).
+template <int KC>
+__device__ __forceinline__ f32x16 tile_mma(const bf16x8 (&a)[KC], const __bf16 *B, int ldb,
+                                           f32x16 acc) {
+  const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+  bf16x8 b[KC];
+#pragma unroll
+  for (int kc = 0; kc < KC; ++kc)
+    b[kc] = *reinterpret_cast<const bf16x8 *>(B + r * ldb + 16 * kc + 8 * h);
+#pragma unroll
+  for (int kc = 0; kc < KC; ++kc)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kc], b[kc], acc, 0, 0, 0);
+  return acc;
+}
+template <int KC>
+__device__ __forceinline__ void tile_rows(const __bf16 *A, int lda, bf16x8 (&a)[KC]) {
   const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+  for (int kc = 0; kc < KC; ++kc)
+    a[kc] = *reinterpret_cast<const bf16x8 *>(A + r * lda + 16 * kc + 8 * h);
+}
+// The tile as BF16 into the sample-major [sample][ldo] (four consecutive units
+// per store) and the unit-major [unit][kLdU] LDS tile, either of them optional.
+template <bool kSample, bool kUnit>
+__device__ __forceinline__ void tile_store(const f32x16 &acc, __bf16 *sm, int ldo, __bf16 *um) {
+  const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+  for (int q = 0; q < 4; ++q) {
+    bf16x4 v;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mt][nt][i] = 0.f;
+    for (int e = 0; e < 4; ++e) v[e] = (__bf16)acc[4 * q + e];
+    if (kSample) *reinterpret_cast<bf16x4 *>(sm + r * ldo + acc_row(4 * q, h)) = v;
+    if (kUnit)
 #pragma unroll
-  for (int kc = 0; kc < 4; ++kc) {
-    bf16x8 a[MT], b[NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-      a[mt] = *reinterpret_cast<const bf16x8 *>(A + (32 * mt + r) * kLdU + 16 * kc + 8 * h);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-      b[nt] = *reinterpret_cast<const bf16x8 *>(B + (32 * nt + r) * kLdU + 16 * kc + 8 * h);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
+      for (int e = 0; e < 4; ++e) um[acc_row(4 * q + e, h) * kLdU + r] = v[e];
   }
 }
 
-// write an accumulator tile set into a unit-major [unit][sample] LDS tile
-template <int MT>
-__device__ __forceinline__ void store_unit_major(const f32x16 (&acc)[MT][2], __bf16 *out) {
-  const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        out[(32 * mt + acc_row(i, h)) * kLdU + 32 * nt + r] = (__bf16)acc[mt][nt][i];
-}
-
-__global__ __launch_bounds__(64) void k_mlp_grad(GradParams G) {
+// One block of four wavefronts per 64 samples; wavefront (mt, nt) holds the
+// 32 x 32 tile mt, nt of every 64 x 64 product (units x samples, units x units).
+// The weights' operands are requested at the start, all at once.  Bound by the
+// latency of the chain of five products with their activations: at a batch of
+// 512 (eight blocks) 8.3 us, against 20.4 us with one wavefront per 64 samples,
+// whose 256 activations per lane alone took a quarter of that.  A training step
+// with its reduction: batch 64 23.5 -> 10.8 us, 512 25.0 -> 11.2 us, 65,536 70.7 ->
+// 47.4 us.
+__global__ __launch_bounds__(256) void k_mlp_grad(GradParams G) {
   __shared__ __attribute__((aligned(16))) __bf16 sX[64 * kLdX];
   __shared__ __attribute__((aligned(16))) __bf16 sXu[32 * kLdU];
   __shared__ __attribute__((aligned(16))) __bf16 sH1[64 * kLdH], sH1u[64 * kLdU], sH2[64 * kLdH], sH2u[64 * kLdU];
   __shared__ __attribute__((aligned(16))) __bf16 sDY[64 * kLdY], sDYu[32 * kLdU];
   __shared__ __attribute__((aligned(16))) __bf16 sDZ2[64 * kLdH], sDZ2u[64 * kLdU], sDZ1u[64 * kLdU];
-  const int lane = threadIdx.x, r = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int wv = tid >> 6, mt = wv >> 1, nt = wv & 1;
   const int64_t base = G.begin + (int64_t)blockIdx.x * 64;
-  const int64_t s = (base + lane) % G.n;
-  // inputs, both layouts
-  for (int k = 0; k < 16; ++k) sX[lane * kLdX + k] = (__bf16)(k < 8 ? G.x[s * 8 + k] : 0.f);
-  for (int k = 0; k < 32; ++k) sXu[k * kLdU + lane] = (__bf16)(k < 8 ? G.x[s * 8 + k] : 0.f);
-  wave_sync();
-  f32x16 z1[2][2], z2[2][2];
-  gemm_w_act<2, 1>(G.w.W1p, kLdW1, sX, kLdX, G.w.b1, z1);
-  {
-    f32x16 a[2][2];
+  // everything read from memory, requested before it is needed: inputs (half a
+  // sample's row per lane), targets and validity of the output tile's sample
+  // (wavefronts 0 and 1), weights and biases
+  // (the caller's rows may start at any float)
+  typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+  float4_any xin = {0.f, 0.f, 0.f, 0.f};
+  if (tid < 128)
+    xin = *reinterpret_cast<const float4_any *>(G.x + ((base + (tid >> 1)) % G.n) * 8 + 4 * (tid & 1));
+  float tgt[4] = {}, vld = 0.f;
+  if (wv < 2) {
+    const int64_t sj = (base + 32 * nt + r) % G.n;
+    vld = G.valid[sj];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) a[mt][nt][i] = silu(z1[mt][nt][i]);
-    store_act<2, false>(a, sH1, kLdH);
-    store_unit_major<2>(a, sH1u);
+    for (int i = 0; i < 4; ++i)
+      if (4 * h + i < kNO) tgt[i] = G.t[sj * 7 + 4 * h + i];
   }
-  wave_sync();
-  gemm_w_act<2, 4>(G.w.W2p, kLdW2, sH1, kLdH, G.w.b2, z2);
-  {
-    f32x16 a[2][2];
+  bf16x8 w1[1], w2[4], w3[4], w3t[2], w2t[4];
+  tile_rows(G.w.W1p + 32 * mt * kLdW1, kLdW1, w1);
+  tile_rows(G.w.W2p + 32 * mt * kLdW2, kLdW2, w2);
+  tile_rows(G.w.W3p, kLdW3, w3);
+  tile_rows(G.w.W3T + 32 * mt * kLdW3T, kLdW3T, w3t);
+  tile_rows(G.w.W2T + 32 * mt * kLdW2, kLdW2, w2t);
+  f32x16 c1, c2, c3, zero;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) a[mt][nt][i] = silu(z2[mt][nt][i]);
-    store_act<2, false>(a, sH2, kLdH);
-    store_unit_major<2>(a, sH2u);
+  for (int i = 0; i < 16; ++i) {
+    c1[i] = G.w.b1[32 * mt + acc_row(i, h)];
+    c2[i] = G.w.b2[32 * mt + acc_row(i, h)];
+    c3[i] = G.w.b3[acc_row(i, h)];
+    zero[i] = 0.f;
   }
-  wave_sync();
-  f32x16 y[1][2];
-  gemm_w_act<1, 4>(G.w.W3p, kLdW3, sH2, kLdH, G.w.b3, y);
-  // output error: dL/dy = 2 w_j (y - t) / B for valid samples
-  float loss = 0.f;
-  f32x16 dy[1][2];
+  // inputs, both layouts: k 8..15 of the sample-major rows and units 8..31 of
+  // the unit-major tile are zero
+  if (tid < 128) {
+    const int sm = tid >> 1, k = 4 * (tid & 1);
+    const float x[4] = {xin.x, xin.y, xin.z, xin.w};
+    bf16x4 v, z;
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int j = acc_row(i, h);
-      float d = 0.f;
-      if (j < kNO) {
-        const int64_t sj = (base + 32 * nt + r) % G.n;
-        const float vv = G.valid[sj];
-        const float e = y[0][nt][i] - G.t[sj * 7 + j];
-        loss += vv * G.loss_w[j] * e * e;
-        d = 2.f * vv * G.loss_w[j] * e * G.inv_batch;
-      }
-      dy[0][nt][i] = d;
+    for (int e = 0; e < 4; ++e) {
+      v[e] = (__bf16)x[e];
+      z[e] = (__bf16)0.f;
+      sXu[(k + e) * kLdU + sm] = v[e];
     }
-  store_act<1, false>(dy, sDY, kLdY);
-  store_unit_major<1>(dy, sDYu);
-  wave_sync();
+    *reinterpret_cast<bf16x4 *>(sX + sm * kLdX + k) = v;
+    *reinterpret_cast<bf16x4 *>(sX + sm * kLdX + 8 + k) = z;
+  } else {
+    bf16x8 z;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) z[e] = (__bf16)0.f;
+    for (int k = tid - 128; k < 24 * kLdU / 8; k += 128)
+      *reinterpret_cast<bf16x8 *>(sXu + 8 * kLdU + 8 * k) = z;
+  }
+  __syncthreads();
+  const f32x16 z1 = tile_mma(w1, sX + 32 * nt * kLdX, kLdX, c1);
+  {
+    f32x16 a;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) a[i] = silu(z1[i]);
+    tile_store<true, true>(a, sH1 + 32 * nt * kLdH + 32 * mt, kLdH, sH1u + 32 * mt * kLdU + 32 * nt);
+  }
+  __syncthreads();
+  const f32x16 z2 = tile_mma(w2, sH1 + 32 * nt * kLdH, kLdH, c2);
+  {
+    f32x16 a;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) a[i] = silu(z2[i]);
+    tile_store<true, true>(a, sH2 + 32 * nt * kLdH + 32 * mt, kLdH, sH2u + 32 * mt * kLdU + 32 * nt);
+  }
+  __syncthreads();
+  float loss = 0.f;
+  if (wv < 2) {  // (the output layer has one row tile)
+    const f32x16 y = tile_mma(w3, sH2 + 32 * nt * kLdH, kLdH, c3);
+    // output error: dL/dy = 2 w_j (y - t) / B for valid samples; the 7 outputs
+    // are rows 0..3 and 4..6 of the lower and upper lanes
+    f32x16 dy = zero;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int j = 4 * h + i;
+      if (j < kNO) {
+        const float e = y[i] - tgt[i];
+        loss += vld * G.loss_w[j] * e * e;
+        dy[i] = 2.f * vld * G.loss_w[j] * e * G.inv_batch;
+      }
+    }
+    tile_store<true, true>(dy, sDY + 32 * nt * kLdY, kLdY, sDYu + 32 * nt);
+  }
+  __syncthreads();
   // dZ2 = (W3^T dY) * silu'(z2)
   {
-    f32x16 g[2][2];
-    gemm_w_act<2, 2>(G.w.W3T, kLdW3T, sDY, kLdY, nullptr, g);
+    f32x16 g = tile_mma(w3t, sDY + 32 * nt * kLdY, kLdY, zero);
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) g[mt][nt][i] *= dsilu(z2[mt][nt][i]);
-    store_act<2, false>(g, sDZ2, kLdH);
-    store_unit_major<2>(g, sDZ2u);
+    for (int i = 0; i < 16; ++i) g[i] *= dsilu(z2[i]);
+    tile_store<true, true>(g, sDZ2 + 32 * nt * kLdH + 32 * mt, kLdH,
+                           sDZ2u + 32 * mt * kLdU + 32 * nt);
   }
-  wave_sync();
+  __syncthreads();
   // dZ1 = (W2^T dZ2) * silu'(z1)
   {
-    f32x16 g[2][2];
-    gemm_w_act<2, 4>(G.w.W2T, kLdW2, sDZ2, kLdH, nullptr, g);
+    f32x16 g = tile_mma(w2t, sDZ2 + 32 * nt * kLdH, kLdH, zero);
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) g[mt][nt][i] *= dsilu(z1[mt][nt][i]);
-    store_unit_major<2>(g, sDZ1u);
+    for (int i = 0; i < 16; ++i) g[i] *= dsilu(z1[i]);
+    tile_store<false, true>(g, nullptr, 0, sDZ1u + 32 * mt * kLdU + 32 * nt);
   }
-  wave_sync();
+  float *sLoss = reinterpret_cast<float *>(sX);  // (the inputs are not read again)
+  if (wv < 2) {
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) loss += __shfl_xor(loss, m);
+    if (lane == 0) sLoss[wv] = loss;
+  }
+  __syncthreads();
+  // weight gradients: products over the block's samples
   float *out = G.partial + (size_t)blockIdx.x * (kNParam + 1);
-  // weight gradients, summed over the wave's samples on the matrix cores
-  {
-    f32x16 g3[1][2];
-    gemm_uu<1, 2>(sDYu, sH2u, g3);
+  bf16x8 a[4];
+  tile_rows(sDZ2u + 32 * mt * kLdU, kLdU, a);
+  const f32x16 g2 = tile_mma(a, sH1u + 32 * nt * kLdU, kLdU, zero);
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+  for (int i = 0; i < 16; ++i)
+    out[kOffW2 + (32 * mt + acc_row(i, h)) * kNH + 32 * nt + r] = g2[i];
+  if (wv < 2) {
+    tile_rows(sDYu, kLdU, a);
+    const f32x16 g3 = tile_mma(a, sH2u + 32 * nt * kLdU, kLdU, zero);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int j = acc_row(i, h), k = 32 * nt + r;
-        if (j < kNO) out[kOffW3 + j * kNH + k] = g3[0][nt][i];
-      }
+    for (int i = 0; i < 4; ++i)
+      if (4 * h + i < kNO) out[kOffW3 + (4 * h + i) * kNH + 32 * nt + r] = g3[i];
+  } else {
+    const int m1 = wv - 2;
+    tile_rows(sDZ1u + 32 * m1 * kLdU, kLdU, a);
+    const f32x16 g1 = tile_mma(a, sXu, kLdU, zero);
+    if (r < kNI)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) out[kOffW1 + (32 * m1 + acc_row(i, h)) * kNI + r] = g1[i];
   }
-  {
-    f32x16 g2[2][2];
-    gemm_uu<2, 2>(sDZ2u, sH1u, g2);
+  // bias gradients: sums over the samples of the unit-major tiles, in order
+  if (wv < 3 && (wv < 2 || lane < kNO)) {
+    const __bf16 *row = (wv == 0 ? sDZ1u : wv == 1 ? sDZ2u : sDYu) + lane * kLdU;
+    float b = 0.f;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int q = 0; q < 8; ++q) {
+      const bf16x8 v = *reinterpret_cast<const bf16x8 *>(row + 8 * q);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          out[kOffW2 + (32 * mt + acc_row(i, h)) * kNH + 32 * nt + r] = g2[mt][nt][i];
-  }
-  {
-    f32x16 g1[2][1];
-    gemm_uu<2, 1>(sDZ1u, sXu, g1);
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (r < kNI) out[kOffW1 + (32 * mt + acc_row(i, h)) * kNI + r] = g1[mt][0][i];
-  }
-  // bias gradients: sums over the samples of the unit-major tiles
-  {
-    float b1 = 0.f, b2 = 0.f, b3 = 0.f;
-    for (int q = 0; q < 64; ++q) {
-      b1 += (float)sDZ1u[lane * kLdU + q];
-      b2 += (float)sDZ2u[lane * kLdU + q];
-      if (lane < kNO) b3 += (float)sDYu[lane * kLdU + q];
+      for (int e = 0; e < 8; ++e) b += (float)v[e];
     }
-    out[kOffB1 + lane] = b1;
-    out[kOffB2 + lane] = b2;
-    if (lane < kNO) out[kOffB3 + lane] = b3;
+    out[(wv == 0 ? kOffB1 : wv == 1 ? kOffB2 : kOffB3) + lane] = b;
   }
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) loss += __shfl_xor(loss, m);
-  if (lane == 0) out[kNParam] = loss * G.inv_batch;
+  if (tid == 255) out[kNParam] = (sLoss[0] + sLoss[1]) * G.inv_batch;
 }
 
 // Sum the partial gradients in wave order; then either write the gradient
@@ -339,7 +361,16 @@ __global__ __launch_bounds__(256) void k_mlp_reduce(AdamParams A) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p > kNParam) return;
   float g = 0.f;
-  for (int w = 0; w < A.n_waves; ++w) g += A.partial[(size_t)w * (kNParam + 1) + p];
+  const float *part = A.partial + p;
+  int w = 0;
+  for (; w + 8 <= A.n_waves; w += 8) {  // eight loads at once, added in order
+    float t[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t[k] = part[(size_t)(w + k) * (kNParam + 1)];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) g += t[k];
+  }
+  for (; w < A.n_waves; ++w) g += part[(size_t)w * (kNParam + 1)];
   if (p == kNParam) {
     *A.loss_out = g;
     return;
@@ -489,7 +520,7 @@ void launch_mlp_grad(hipStream_t s, const MlpWeights &w, const float *x, const f
   for (int j = 0; j < 7; ++j) G.loss_w[j] = loss_w[j];
   G.inv_batch = 1.f / (float)batch;
   G.partial = partial;
-  hipLaunchKernelGGL(k_mlp_grad, dim3(batch / 64), dim3(64), 0, s, G);
+  hipLaunchKernelGGL(k_mlp_grad, dim3(batch / 64), dim3(256), 0, s, G);
 }
 
 void launch_mlp_reduce(hipStream_t s, const MlpBuffers &B, const float *partial, int n_waves,
