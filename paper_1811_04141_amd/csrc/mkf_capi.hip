@@ -160,6 +160,7 @@ struct mkf_ctx {
   int device = 0;  // the device current at mkf_create
   std::string arch;
   mkf_tuning tuning{2, 8, 0, 0, 0};
+  bool tuned = false;  // a tuning was set: its launch shape is used as it is
 
   // learned surrogate: master weights, Adam moments, BF16 images, counters
   DevBuf d_mlp_param, d_mlp_m, d_mlp_v, d_W1p, d_W2p, d_W3p, d_W2T, d_W3T, d_mb1, d_mb2, d_mb3;
@@ -868,6 +869,27 @@ mkf_status mkf_get_seed_states(mkf_ctx *c, float *par, float *cov, int32_t *ok,
   return MKF_OK;
 }
 
+// Launch shape of the persistent find where none was set: as many waves per SIMD
+// as its tiles fill, from two up to three, the most that run without spilling
+// much (2 and 3 waves: 100 events x 5,000 seeds 1.79 and 1.39 ms, 24 such events
+// 0.427 and 0.371 ms, but 2 events 0.098 and 0.102 ms); four where that takes
+// all tiles at once (8 events, 4,000 tiles: 0.142 ms, 0.178 at three; 20 events
+// of 2,000 seeds with material and field 0.275 and 0.302 ms), though not with the
+// surrogate, which spills far more there.  No more blocks than are resident: the
+// starting value of eight per CU left the blocks beyond them to a second turn
+// (1.85 ms for 1.79 at two waves).
+static void launch_shape(const mkf_ctx *c, int &waves, int &blocks_per_cu) {
+  waves = c->tuning.waves_per_simd;
+  blocks_per_cu = c->tuning.blocks_per_cu;
+  if (c->tuned) return;
+  const int seeds = c->cfg.n_cand > 6 ? 8 : 10;
+  const int64_t tiles = (c->n_seeds + seeds - 1) / seeds, simds = 4 * (int64_t)c->n_cu;
+  const bool all_in_four = tiles > 3 * simds && tiles <= 4 * simds;
+  waves = tiles <= 2 * simds ? 2
+          : all_in_four && !(c->cfg.flags & MKF_F_SURROGATE) ? 4 : 3;
+  blocks_per_cu = waves;
+}
+
 // Queue the whole find on the context stream.  main_a/main_b (may be
 // null) bracket the layer-step kernels.
 static int enqueue_find(mkf_ctx *c, const FindParams &P, hipEvent_t main_a, hipEvent_t main_b) {
@@ -876,9 +898,10 @@ static int enqueue_find(mkf_ctx *c, const FindParams &P, hipEvent_t main_a, hipE
   ++launches;
   if (c->cfg.flags & MKF_F_BATCHED) {
     if (main_a) (void)hipEventRecord(main_a, c->stream);
-    launch_find_persistent(c->stream, P, c->tuning.blocks_per_cu * c->n_cu,
-                           c->tuning.waves_per_simd, (c->cfg.flags & MKF_F_SURROGATE) != 0,
-                           c->tuning.lane_group);
+    int waves, blocks_per_cu;
+    launch_shape(c, waves, blocks_per_cu);
+    launch_find_persistent(c->stream, P, blocks_per_cu * c->n_cu, waves,
+                           (c->cfg.flags & MKF_F_SURROGATE) != 0, c->tuning.lane_group);
     ++launches;
     c->stats.main_launches = 1;
   } else {
@@ -1256,6 +1279,7 @@ mkf_status apply_tuning(mkf_ctx *c, const mkf_tuning &t) {
   const bool rebin =
       t.phi_bin_shift != c->tuning.phi_bin_shift || t.q_bin_shift != c->tuning.q_bin_shift;
   c->tuning = t;
+  c->tuned = true;
   drop_graph(c);
   if (!rebin || c->n_layers == 0) return MKF_OK;
   mkf_status st = upload_layers(c);
@@ -1322,6 +1346,7 @@ mkf_status mkf_autotune(mkf_ctx *c, int32_t repeats, const char *cache_path, mkf
   const uint32_t flags = c->cfg.flags;
   c->cfg.flags &= ~MKF_F_GRAPH;  // time eager launches
   const mkf_tuning keep = c->tuning;
+  const bool keep_tuned = c->tuned;
   mkf_tuning win = c->tuning;
   float win_ms = 1e30f;
   mkf_status st = MKF_OK;
@@ -1360,6 +1385,7 @@ mkf_status mkf_autotune(mkf_ctx *c, int32_t repeats, const char *cache_path, mkf
   if (st != MKF_OK) {
     std::string e = c->err;
     (void)apply_tuning(c, keep);
+    c->tuned = keep_tuned;
     c->err = e;
     return st;
   }

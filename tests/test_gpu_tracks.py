@@ -16,10 +16,12 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-@pytest.mark.parametrize("n", [1, CHUNK - 1, CHUNK, CHUNK + 1, 3 * CHUNK - 5, 9 * CHUNK + 7])
+@pytest.mark.parametrize("n", [1, CHUNK - 1, CHUNK, CHUNK + 1, 20481, 3 * CHUNK - 5,
+                               30721, 40960, 40961, 9 * CHUNK + 7])
 def test_records_in_seed_order(n):
     """An event's seeds repeated to n: every record is its seed's own, whatever
-    the number of chunks, also into a longer and into a shorter array."""
+    the number of chunks and the launch shape the find takes for n seeds, also
+    into a longer and into a shorter array."""
     from paper_1811_04141_amd import mkf
     w = small_barrel()
     b = generate(w)
