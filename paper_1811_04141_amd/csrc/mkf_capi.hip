@@ -120,8 +120,8 @@ struct mkf_ctx {
   int n_events = 0;
   int64_t n_hits = 0;
   std::vector<int64_t> ev_off;
-  DevBuf d_ev_off, d_x, d_y, d_z, d_vu, d_vv, d_layer;
-  DevBuf d_hit_bin, d_counts, d_fill, d_bin_start, d_scan_tmp, d_sorted, d_byorig, d_bad;
+  DevBuf d_ev_off, d_x, d_y, d_z, d_vu, d_vv, d_layer;  // (the arrays: host inputs on their way)
+  DevBuf d_bin_rank, d_counts, d_bin_start, d_scan_tmp, d_sorted, d_byorig, d_raw;
 
   // seeds
   int64_t n_seeds = 0;
@@ -170,8 +170,8 @@ struct mkf_ctx {
   // fit scratch (host-side inputs are staged here)
   ~mkf_ctx() {
     DevBuf *all[] = {&d_layers, &d_regions, &d_mat, &d_ev_off, &d_x, &d_y, &d_z, &d_vu, &d_vv, &d_layer,
-                     &d_hit_bin, &d_counts, &d_fill, &d_bin_start, &d_scan_tmp, &d_sorted,
-                     &d_byorig, &d_bad, &d_seed_event, &d_seed_hits, &d_seed_state, &d_seed_ok,
+                     &d_bin_rank, &d_counts, &d_bin_start, &d_scan_tmp, &d_sorted,
+                     &d_byorig, &d_raw, &d_seed_event, &d_seed_hits, &d_seed_state, &d_seed_ok,
                      &d_plan_len, &d_plan, &d_cell_counts, &d_cell_start, &d_cell_rank, &d_order, &d_pos, &d_pstate, &d_pinfo,
                      &d_pevent, &d_pplan, &d_cand, &d_fin_key, &d_fin_rec, &d_fin_meta,
                      &d_bp, &d_out, &d_mlp_param, &d_mlp_m, &d_mlp_v, &d_W1p,
@@ -227,6 +227,12 @@ DevCfg dev_cfg(const mkf_config &c) {
   return d;
 }
 
+bool has_stereo(const mkf_ctx *c) {
+  for (int i = 0; i < c->n_layers; ++i)
+    if (c->user_layers[i].stereo != 0.f) return true;
+  return false;
+}
+
 FindParams params(mkf_ctx *c) {
   FindParams P{};
   P.layers = c->d_layers.as<DevLayer>();
@@ -236,12 +242,7 @@ FindParams params(mkf_ctx *c) {
   P.cfg.field = c->field;
   P.n_events = c->n_events;
   P.ev_off = c->d_ev_off.as<int64_t>();
-  P.hx = c->d_x.as<float>();
-  P.hy = c->d_y.as<float>();
-  P.hz = c->d_z.as<float>();
-  P.hvu = c->d_vu.as<float>();
-  P.hvv = c->d_vv.as<float>();
-  P.hlayer = c->d_layer.as<int>();
+  P.raw = has_stereo(c) ? c->d_raw.as<float2>() : nullptr;
   P.sorted = c->d_sorted.as<HitRec>();
   P.byorig = c->d_byorig.as<HitRec>();
   P.bin_start = c->d_bin_start.as<int>();
@@ -396,7 +397,6 @@ mkf_status mkf_create(const mkf_config *cfg, void *stream, mkf_ctx **out) {
   if (e == hipSuccess) e = hipEventCreate(&c->ev_b);
   if (e == hipSuccess) e = hipEventCreate(&c->ev_m0);
   if (e == hipSuccess) e = hipEventCreate(&c->ev_m1);
-  if (e == hipSuccess) e = c->d_bad.ensure(sizeof(int));
   if (e == hipSuccess)
     e = hipHostMalloc(reinterpret_cast<void **>(&c->h_cnt),
                       sizeof(unsigned long long) * kFindWords +
@@ -486,33 +486,35 @@ mkf_status upload_layers(mkf_ctx *c) {
   return MKF_OK;
 }
 
-// The binned hit index of the loaded hits (count, scan, scatter), for the
-// current layer records.
-mkf_status build_index(mkf_ctx *c) {
+// The binned hit index (records and counts, scan, scatter) for the current
+// layer records: of the given hits, or (in.x null) again of the loaded ones.
+mkf_status build_index(mkf_ctx *c, const HitArrays &in) {
   const int64_t n_hits = c->n_hits;
   const int64_t total_bins = (int64_t)c->n_events * c->bins_per_event;
   if (total_bins >= ((int64_t)1 << 31) - 1)
     return fail(c, MKF_E_CAPACITY, "events x bins exceed the index size");
-  HIP_TRY(c, c->d_hit_bin.ensure(sizeof(int) * (size_t)std::max<int64_t>(n_hits, 1)));
+  const size_t H = (size_t)std::max<int64_t>(n_hits, 1);
+  HIP_TRY(c, c->d_bin_rank.ensure(sizeof(int2) * H));
   HIP_TRY(c, c->d_counts.ensure(sizeof(int) * (size_t)std::max<int64_t>(total_bins, 1)));
-  HIP_TRY(c, c->d_fill.ensure(sizeof(int) * (size_t)std::max<int64_t>(total_bins, 1)));
   HIP_TRY(c, c->d_bin_start.ensure(sizeof(int) * (size_t)(total_bins + 1)));
   HIP_TRY(c, c->d_scan_tmp.ensure(sizeof(int) * (size_t)scan_tmp_words(total_bins)));
-  HIP_TRY(c, c->d_sorted.ensure(sizeof(HitRec) * (size_t)(std::max<int64_t>(n_hits, 1) + kHitPad)));
-  HIP_TRY(c, c->d_byorig.ensure(sizeof(HitRec) * (size_t)std::max<int64_t>(n_hits, 1)));
+  HIP_TRY(c, c->d_sorted.ensure(sizeof(HitRec) * (H + kHitPad)));
+  HIP_TRY(c, c->d_byorig.ensure(sizeof(HitRec) * H));
+  if (has_stereo(c)) HIP_TRY(c, c->d_raw.ensure(sizeof(float2) * H));
+  const FindParams P = params(c);
+  *c->h_bad = 0;
   HIP_TRY(c, hipEventRecord(c->ev_a, c->stream));
   launch_fill_i32(c->stream, c->d_counts.as<int>(), total_bins, 0);
-  launch_fill_i32(c->stream, c->d_fill.as<int>(), total_bins, 0);
-  FindParams P = params(c);
-  launch_hit_bins(c->stream, P, n_hits, c->d_layer.as<int>(), c->d_hit_bin.as<int>(),
-                  c->d_counts.as<int>());
+  launch_hits_in(c->stream, P, n_hits, in, c->d_byorig.as<HitRec>(),
+                 has_stereo(c) ? c->d_raw.as<float2>() : nullptr, c->d_bin_rank.as<int2>(),
+                 c->d_counts.as<int>(), c->h_bad);
   launch_scan(c->stream, c->d_counts.as<int>(), c->d_bin_start.as<int>(), total_bins,
               c->d_scan_tmp.as<int>());
-  launch_scatter(c->stream, P, n_hits, c->d_hit_bin.as<int>(), c->d_fill.as<int>(),
-                 c->d_sorted.as<HitRec>(), c->d_byorig.as<HitRec>());
+  launch_scatter(c->stream, P, n_hits, c->d_bin_rank.as<int2>(), c->d_sorted.as<HitRec>());
   HIP_TRY(c, hipGetLastError());
   HIP_TRY(c, hipEventRecord(c->ev_b, c->stream));
-  HIP_TRY(c, hipEventSynchronize(c->ev_b));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (*c->h_bad) return fail(c, MKF_E_ARG, "hits: non-finite value, variance <= 0 or bad layer");
   float ms = 0.f;
   HIP_TRY(c, hipEventElapsedTime(&ms, c->ev_a, c->ev_b));
   c->stats.index_ms = ms;
@@ -692,26 +694,21 @@ mkf_status mkf_load_hits(mkf_ctx *c, int32_t n_events, const int64_t *ev_off, co
   const size_t fb = sizeof(float) * (size_t)n_hits;
   mkf_status st;
   if ((st = stage_in(c, c->d_ev_off, ev_off, sizeof(int64_t) * (n_events + 1), MKF_MEM_HOST))) return st;
-  if ((st = stage_in(c, c->d_x, x, fb, mem))) return st;
-  if ((st = stage_in(c, c->d_y, y, fb, mem))) return st;
-  if ((st = stage_in(c, c->d_z, z, fb, mem))) return st;
-  if ((st = stage_in(c, c->d_vu, var_u, fb, mem))) return st;
-  if ((st = stage_in(c, c->d_vv, var_v, fb, mem))) return st;
-  if ((st = stage_in(c, c->d_layer, layer, sizeof(int) * (size_t)n_hits, mem))) return st;
-  if (mem == MKF_MEM_DEVICE && n_hits > 0) {
-    HIP_TRY(c, hipMemsetAsync(c->d_bad.ptr, 0, sizeof(int), c->stream));
-    launch_validate_hits(c->stream, n_hits, c->d_x.as<float>(), c->d_y.as<float>(),
-                         c->d_z.as<float>(), c->d_vu.as<float>(), c->d_vv.as<float>(),
-                         c->d_layer.as<int>(), c->n_layers, c->d_bad.as<int>());
-    int bad = 0;
-    HIP_TRY(c, hipMemcpyAsync(&bad, c->d_bad.ptr, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (bad) return fail(c, MKF_E_ARG, "hits: non-finite value, variance <= 0 or bad layer");
+  HitArrays in{x, y, z, var_u, var_v, layer};
+  if (mem == MKF_MEM_HOST && n_hits > 0) {
+    if ((st = stage_in(c, c->d_x, x, fb, mem))) return st;
+    if ((st = stage_in(c, c->d_y, y, fb, mem))) return st;
+    if ((st = stage_in(c, c->d_z, z, fb, mem))) return st;
+    if ((st = stage_in(c, c->d_vu, var_u, fb, mem))) return st;
+    if ((st = stage_in(c, c->d_vv, var_v, fb, mem))) return st;
+    if ((st = stage_in(c, c->d_layer, layer, sizeof(int) * (size_t)n_hits, mem))) return st;
+    in = HitArrays{c->d_x.as<float>(),  c->d_y.as<float>(),  c->d_z.as<float>(),
+                   c->d_vu.as<float>(), c->d_vv.as<float>(), c->d_layer.as<int>()};
   }
   c->n_events = n_events;
   c->n_hits = n_hits;
   c->ev_off.assign(ev_off, ev_off + n_events + 1);
-  if ((st = build_index(c))) return st;
+  if ((st = build_index(c, in))) return st;
   c->stage = kHits;
   c->n_seeds = 0;
   return MKF_OK;
@@ -1283,7 +1280,7 @@ mkf_status apply_tuning(mkf_ctx *c, const mkf_tuning &t) {
   drop_graph(c);
   if (!rebin || c->n_layers == 0) return MKF_OK;
   mkf_status st = upload_layers(c);
-  if (st == MKF_OK && c->stage >= kHits) st = build_index(c);
+  if (st == MKF_OK && c->stage >= kHits) st = build_index(c, HitArrays{});
   return st;
 }
 

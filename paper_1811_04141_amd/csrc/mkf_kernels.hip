@@ -1254,12 +1254,14 @@ __global__ __launch_bounds__(kSeedBlock) void k_seed(
   int hl[3];
   for (int k = 0; k < 3; ++k) {
     const int64_t g = e0 + sh[k];
-    hx[k] = P.hx[g];
-    hy[k] = P.hy[g];
-    hz[k] = P.hz[g];
-    hvu[k] = P.hvu[g];
-    hvv[k] = P.hvv[g];
-    hl[k] = P.hlayer[g];
+    const HitRec h = P.byorig[g];
+    const float2 var = P.raw ? P.raw[g] : make_float2(h.vu, h.vv);
+    hx[k] = h.x;
+    hy[k] = h.y;
+    hz[k] = h.z;
+    hvu[k] = var.x;
+    hvv[k] = var.y;
+    hl[k] = h.layer;
   }
   const double mkb = P.cfg.mkb, l_min = P.cfg.l_min, edge = P.cfg.edge_margin;
   int ok = 0;
@@ -2064,37 +2066,73 @@ __global__ __launch_bounds__(256) void k_clean_decide(FindParams P, const int *s
   if (keep) atomicAdd(n_keep, 1);
 }
 
-__global__ __launch_bounds__(256) void k_hit_bins(FindParams P, int n_events, int64_t n_hits,
-                                                  const int *layer, int *hit_bin, int *counts) {
-  __shared__ DevLayer sl[kMaxLayers];
-  stage_layers(P, sl);
-  __syncthreads();
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_hits) return;
-  const int e = event_of(P.ev_off, n_events, i);
-  const int b = e * P.bins_per_event + bin_of(sl[layer[i]], P.hx[i], P.hy[i], P.hz[i]);
-  hit_bin[i] = b;
-  atomicAdd(&counts[b], 1);
+// Event of hit i, known to lie in events e_lo .. e_hi (a block's hits span few).
+__device__ __forceinline__ int event_between(const int64_t *ev_off, int e_lo, int e_hi, int64_t i) {
+  while (e_lo < e_hi) {  // ev_off[e_lo] <= i < ev_off[e_hi + 1]
+    const int mid = (e_lo + e_hi + 1) >> 1;
+    if (ev_off[mid] <= i) e_lo = mid; else e_hi = mid - 1;
+  }
+  return e_lo;
 }
 
-__global__ __launch_bounds__(256) void k_hit_scatter(FindParams P, int n_events, int64_t n_hits,
-                                                     const int *hit_bin, int *fill,
-                                                     HitRec *sorted, HitRec *byorig) {
+// One lane per hit: record, check, bin.  Counting gives each hit its rank in
+// its bin, so that the scatter needs no second count.  Bound by HBM and the
+// atomics' look-ups: 24 B read, 40 B written and one counter per hit.  7.6
+// million hits of 100 events: 0.37 ms, the scatter 0.25; the whole call 0.69 ms,
+// against 1.10 when the arrays were copied, checked, binned and scattered one
+// after the other.  (An XCD for each event's blocks, so that its L2 gathers the
+// scattered records: 0.35 and 0.27 ms, no gain.)
+template <bool kIn>
+__global__ __launch_bounds__(256) void k_hits(FindParams P, int64_t n_hits, HitArrays in,
+                                              HitRec *byorig, float2 *raw, int2 *bin_rank,
+                                              int *counts, int *bad) {
+  __shared__ DevLayer sl[kMaxLayers];
+  __shared__ int s_ev[2];
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x;
+  stage_layers(P, sl);
+  if (threadIdx.x < 2)
+    s_ev[threadIdx.x] =
+        event_of(P.ev_off, P.n_events, threadIdx.x == 0 ? i0 : min(i0 + 255, n_hits - 1));
+  __syncthreads();
+  const int64_t i = i0 + threadIdx.x;
+  if (i >= n_hits) return;
+  const int e = event_between(P.ev_off, s_ev[0], s_ev[1], i);
+  HitRec h;
+  bool good = true;
+  if constexpr (kIn) {
+    const float vu = in.vu[i], vv = in.vv[i];
+    h.x = in.x[i];
+    h.y = in.y[i];
+    h.z = in.z[i];
+    h.layer = in.layer[i];
+    good = isfinite(h.x) && isfinite(h.y) && isfinite(h.z) && isfinite(vu) && isfinite(vv) &&
+           vu > 0.f && vv > 0.f && h.layer >= 0 && h.layer < P.n_layers;
+    if (good) {
+      const DevLayer &L = sl[h.layer];
+      hit_cov(L.cs, L.sn, vu, vv, h.vu, h.vv, h.vuv);
+      h.orig = (int)(i - P.ev_off[e]);
+      byorig[i] = h;
+      if (raw) raw[i] = make_float2(vu, vv);
+    } else {
+      *bad = 1;
+    }
+  } else {
+    h = byorig[i];
+  }
+  int b = -1, rank = 0;
+  if (good) {
+    b = e * P.bins_per_event + bin_of(sl[h.layer], h.x, h.y, h.z);
+    rank = atomicAdd(&counts[b], 1);
+  }
+  bin_rank[i] = make_int2(b, rank);
+}
+
+__global__ __launch_bounds__(256) void k_hit_scatter(FindParams P, int64_t n_hits,
+                                                     const int2 *bin_rank, HitRec *sorted) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_hits) return;
-  const int e = event_of(P.ev_off, n_events, i);
-  const int b = hit_bin[i];
-  const int slot = P.bin_start[b] + atomicAdd(&fill[b], 1);
-  HitRec h;
-  h.x = P.hx[i];
-  h.y = P.hy[i];
-  h.z = P.hz[i];
-  const DevLayer &L = P.layers[P.hlayer[i]];
-  hit_cov(L.cs, L.sn, P.hvu[i], P.hvv[i], h.vu, h.vv, h.vuv);
-  h.orig = (int)(i - P.ev_off[e]);
-  h.pad1 = 0;
-  sorted[slot] = h;
-  byorig[i] = h;
+  const int2 br = bin_rank[i];
+  if (br.x >= 0) sorted[P.bin_start[br.x] + br.y] = P.byorig[i];
 }
 
 // Exclusive sums in two launches: a block adds up its chunk of tiles; then
@@ -2340,7 +2378,7 @@ __device__ __forceinline__ bool backfit_seq(const FindParams &P, const int *hit,
     return code >= MKF_HIT_MISS;  // not crossed, or after the track ended
   }
   code = sh[t];
-  lid = P.hlayer[ev_base + code];
+  lid = P.byorig[ev_base + code].layer;
   return true;
 }
 
@@ -2524,7 +2562,7 @@ __global__ __launch_bounds__(256) void k_smooth_fwd(FindParams P, const int *see
     for (int m = 0; m < 6; ++m) at(0, kSmFilt + m) = p[m];
 #pragma unroll
     for (int m = 0; m < 21; ++m) at(0, kSmFilt + 6 + m) = c[m];
-    at(0, kSmLayer) = __int_as_float(P.hlayer[ev_base + sh[2]]);
+    at(0, kSmLayer) = __int_as_float(P.byorig[ev_base + sh[2]].layer);
     n = 1;
     for (int s = 0; s < plen; ++s) {
       const int code = hit[s];
@@ -2771,25 +2809,18 @@ __global__ __launch_bounds__(256) void k_smooth_bwd(FindParams P, const float *w
   out_n[seed] = n;
 }
 
-__global__ __launch_bounds__(256) void k_validate_hits(int64_t n, const float *x, const float *y,
-                                                       const float *z, const float *vu,
-                                                       const float *vv, const int *layer,
-                                                       int n_layers, int *bad) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const bool good = isfinite(x[i]) && isfinite(y[i]) && isfinite(z[i]) && isfinite(vu[i]) &&
-                    isfinite(vv[i]) && vu[i] > 0.f && vv[i] > 0.f && layer[i] >= 0 &&
-                    layer[i] < n_layers;
-  if (!good) atomicOr(bad, 1);
-}
-
 __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
 }
-__global__ void k_fill_i32(int *p, int64_t n, int v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+// (p 16-byte aligned)
+__global__ __launch_bounds__(256) void k_fill_i32(int *p, int64_t n, int v) {
+  const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  if (i + 4 <= n) {
+    *reinterpret_cast<int4 *>(p + i) = make_int4(v, v, v, v);
+  } else {
+    for (int64_t k = i; k < n; ++k) p[k] = v;
+  }
 }
 
 // The checked find's invariants of one seed's result record: a seed whose
@@ -2821,7 +2852,7 @@ __global__ __launch_bounds__(256) void k_check_results(FindParams P) {
         const int lid = P.pplan[(size_t)pos * kMaxPlan + s];
         if (h >= 0) {
           if (stopped || h >= nev) bad = 1;
-          else if (P.hlayer[base + h] != lid) bad = 1;
+          else if (P.byorig[base + h].layer != lid) bad = 1;
           ++found;
         } else if (h == MKF_HIT_MISS) {
           bad |= stopped;
@@ -2857,18 +2888,22 @@ __global__ __launch_bounds__(256) void k_check_results(FindParams P) {
 
 static inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-void launch_hit_bins(hipStream_t s, const FindParams &P, int64_t n_hits, const int *layer,
-                     int *hit_bin, int *counts) {
+void launch_hits_in(hipStream_t s, const FindParams &P, int64_t n_hits, const HitArrays &in,
+                    HitRec *byorig, float2 *raw, int2 *bin_rank, int *counts, int *bad) {
   if (n_hits == 0) return;
-  hipLaunchKernelGGL(k_hit_bins, dim3(blocks_for(n_hits, 256)), dim3(256), 0, s, P, P.n_events,
-                     n_hits, layer, hit_bin, counts);
+  const dim3 grid(blocks_for(n_hits, 256));
+  if (in.x)
+    hipLaunchKernelGGL(k_hits<true>, grid, dim3(256), 0, s, P, n_hits, in, byorig, raw, bin_rank,
+                       counts, bad);
+  else
+    hipLaunchKernelGGL(k_hits<false>, grid, dim3(256), 0, s, P, n_hits, in, byorig, raw, bin_rank,
+                       counts, bad);
 }
 
-void launch_scatter(hipStream_t s, const FindParams &P, int64_t n_hits, const int *hit_bin,
-                    int *fill, HitRec *sorted, HitRec *byorig) {
+void launch_scatter(hipStream_t s, const FindParams &P, int64_t n_hits, const int2 *bin_rank,
+                    HitRec *sorted) {
   if (n_hits == 0) return;
-  hipLaunchKernelGGL(k_hit_scatter, dim3(blocks_for(n_hits, 256)), dim3(256), 0, s, P,
-                     P.n_events, n_hits, hit_bin, fill, sorted, byorig);
+  hipLaunchKernelGGL(k_hit_scatter, dim3(blocks_for(n_hits, 256)), dim3(256), 0, s, P, n_hits, bin_rank, sorted);
 }
 
 void launch_scan(hipStream_t s, const int *in, int *out, int64_t n, int *tmp) {
@@ -3097,21 +3132,13 @@ void launch_clean_decide(hipStream_t s, const FindParams &P, const int *seed_hit
                      seed_hits, seed_chi2, hbuf, off, list, cc, out_keep, n_keep);
 }
 
-void launch_validate_hits(hipStream_t s, int64_t n, const float *x, const float *y,
-                          const float *z, const float *vu, const float *vv, const int *layer,
-                          int n_layers, int *bad) {
-  if (n == 0) return;
-  hipLaunchKernelGGL(k_validate_hits, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, x, y, z, vu,
-                     vv, layer, n_layers, bad);
-}
-
 void launch_fill_u64(hipStream_t s, unsigned long long *p, int64_t n, unsigned long long v) {
   if (n == 0) return;
   hipLaunchKernelGGL(k_fill_u64, dim3(blocks_for(n, 256)), dim3(256), 0, s, p, n, v);
 }
 void launch_fill_i32(hipStream_t s, int *p, int64_t n, int v) {
   if (n == 0) return;
-  hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(n, 256)), dim3(256), 0, s, p, n, v);
+  hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(n, 1024)), dim3(256), 0, s, p, n, v);
 }
 
 }  // namespace mkf

@@ -19,7 +19,7 @@ struct alignas(16) HitRec {
   float vv;
   int orig;  // event-local index in the caller's order
   float vuv;
-  int pad1;
+  int layer;
 };
 
 // Steering of one tracking region: seeds with eta_lo <= eta < eta_hi
@@ -52,10 +52,9 @@ struct FindParams {
   // hits
   int n_events;
   const int64_t *ev_off;   // n_events + 1
-  const float *hx, *hy, *hz, *hvu, *hvv;  // caller order, all events
-  const int *hlayer;
+  const float2 *raw;       // the caller's variances, or null where vu, vv are they (no stereo layer)
   const HitRec *sorted;    // binned
-  const HitRec *byorig;    // the same records in the caller's order
+  const HitRec *byorig;    // the same records in the caller's order, all events
   const int *bin_start;    // n_events * bins_per_event + 1
   int bins_per_event;
   // seeds, by seed id (written by the seed kernel)
@@ -168,15 +167,23 @@ void launch_clean_fill(hipStream_t s, const FindParams &P, const int *hbuf, cons
 void launch_clean_decide(hipStream_t s, const FindParams &P, const int *seed_hits,
                          const float *seed_chi2, const int *hbuf, const int *off,
                          const int *list, const DevCleaning &cc, int *out_keep, int *n_keep);
-void launch_hit_bins(hipStream_t s, const FindParams &P, int64_t n_hits, const int *layer,
-                     int *hit_bin, int *counts);
+// The hits as the caller gave them (x == nullptr: the records already in byorig)
+// into records, checked (a bad one sets *bad, host memory the device can write),
+// and their bins counted: bin_rank[i] is hit i's bin and its rank there (a bad
+// hit: bin -1).
+struct HitArrays {
+  const float *x, *y, *z, *vu, *vv;
+  const int *layer;
+};
+void launch_hits_in(hipStream_t s, const FindParams &P, int64_t n_hits, const HitArrays &in,
+                    HitRec *byorig, float2 *raw, int2 *bin_rank, int *counts, int *bad);
 // exclusive sums of in[0 .. n) into out[0 .. n], out[n] the total; tmp holds
 // scan_tmp_words(n) words
 constexpr int64_t kScanTile = 1024;
 constexpr int64_t scan_tmp_words(int64_t n) { return n / (4 * kScanTile) + 1; }
 void launch_scan(hipStream_t s, const int *in, int *out, int64_t n, int *tmp);
-void launch_scatter(hipStream_t s, const FindParams &P, int64_t n_hits, const int *hit_bin,
-                    int *fill, HitRec *sorted, HitRec *byorig);
+void launch_scatter(hipStream_t s, const FindParams &P, int64_t n_hits, const int2 *bin_rank,
+                    HitRec *sorted);
 // A seed's place in the processing order is found by a counting sort over
 // cells of event group, plan length and direction (kDirCells cells of theta
 // and phi): by group, then longest plan first (persistent form), or longest
@@ -257,9 +264,6 @@ void launch_mlp_reduce(hipStream_t s, const MlpBuffers &B, const float *partial,
 void launch_mlp_images(hipStream_t s, const MlpBuffers &B);
 void launch_mlp_infer(hipStream_t s, const MlpWeights &w, int64_t n, const float *x, float *y);
 
-void launch_validate_hits(hipStream_t s, int64_t n, const float *x, const float *y,
-                          const float *z, const float *vu, const float *vv, const int *layer,
-                          int n_layers, int *bad);
 void launch_fill_u64(hipStream_t s, unsigned long long *p, int64_t n, unsigned long long v);
 void launch_fill_i32(hipStream_t s, int *p, int64_t n, int v);
 
