@@ -163,6 +163,34 @@ struct Cand {
   bool active;
 };
 
+// The kernels outside the find that fit (seeds, tracks, backwards, smoothing)
+// come in two forms, as the find does: kExt with the material map and the
+// parameterised field, and without, where the crossing is the helix's and the
+// scattering angle constant.  The uniform form keeps the stepped crossing's and
+// the map's registers out of the kernel (fit 163 -> 112, backward tail 134 -> 110,
+// smoothing 204 -> 157, seeds 396 -> 310) and takes the angle's sine and cosine
+// once: 1 million fits of 26 hits 616 -> 575 us, backward fit of 500,000 tracks 436
+// -> 387 us (its FP64 part at two waves per SIMD, ten registers spilled; 414 at
+// one), 500,000 seeds 418 -> 378 us.
+template <bool kExt>
+__device__ __forceinline__ const DevField *field_of(const DevCfg &cfg) {
+  return kExt ? &cfg.field : nullptr;
+}
+inline bool extended(const DevCfg &cfg) { return cfg.mat.tab || cfg.field.on; }
+// a crossed layer's material on the way out; sth, cth: sine and cosine of p's
+// theta, at hand from the propagation, which leaves theta as it was
+template <bool kExt, typename T>
+__device__ __forceinline__ void layer_material(const DevCfg &cfg, int kind, T *p, T *c, T sth,
+                                               T cth, T *j33 = nullptr, T *j35 = nullptr) {
+  if constexpr (kExt) {
+    material<T>(cfg, kind, p, c, T(1), j33, j35);
+  } else {
+    add_ms(p, T(cfg.ms_var), c, sth, cth);
+    if (j33) *j33 = T(1);
+    if (j35) *j35 = T(0);
+  }
+}
+
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // ------------------------------------------------------------ records
@@ -1224,6 +1252,7 @@ __global__ __launch_bounds__(256) void k_validate_seeds(FindParams P, const int 
   if (!good) *bad = 1;
 }
 
+template <bool kExt>
 __global__ __launch_bounds__(kSeedBlock) void k_seed(
     FindParams P, const int *src_event, const int *src_hits, int *seed_event, int *seed_hits,
     float *seed_state, int *seed_ok, int *plan_len, int8_t *plan, float *seed_chi2,
@@ -1281,7 +1310,7 @@ __global__ __launch_bounds__(kSeedBlock) void k_seed(
     const bool ccw = turn > 0.0;  // omega > 0
     // omega = mkb * ipt and |omega| = 1/rho; a parameterised field is taken
     // at the middle hit
-    const double mkb_s = P.cfg.field.on ? field_mkb(P.cfg.field, hx[1], hy[1], hz[1]) : mkb;
+    const double mkb_s = kExt && P.cfg.field.on ? field_mkb(P.cfg.field, hx[1], hy[1], hz[1]) : mkb;
     if (mkb_s == 0.0) break;
     const double ipt = (ccw ? 1.0 : -1.0) / (mkb_s * rho);
     const double r1x = hx[0] - cx, r1y = hy[0] - cy;
@@ -1299,14 +1328,15 @@ __global__ __launch_bounds__(kSeedBlock) void k_seed(
       if (k > 0) {
         PropT<double> pr;
         if (propagate<true, double>(p, c, L, mkb, l_min, false, 0.0, pr, 0.0, nullptr, nullptr,
-                                    &P.cfg.field) != kOk) {
+                                    field_of<kExt>(P.cfg)) != kOk) {
           good = false;
           break;
         }
         for (int q = 0; q < 6; ++q) p[q] = pr.p[q];
         for (int q = 0; q < 21; ++q) c[q] = pr.c[q];
       }
-      material<double>(P.cfg, L.kind, p, c, 1.0);
+      if constexpr (kExt) material<double>(P.cfg, L.kind, p, c, 1.0);
+      else add_ms(p, (double)P.cfg.ms_var, c);
       FrameT<double> f;
       make_frame(p, c, L.kind, f);
       double u, v;
@@ -1343,7 +1373,7 @@ __global__ __launch_bounds__(kSeedBlock) void k_seed(
       if (L == hl[0] || L == hl[1] || L == hl[2]) continue;
       PropT<double> pr;
       if (propagate<false, double>(p, nullptr, sl[L], mkb, l_min, true, edge, pr, 0.0, nullptr,
-                                   nullptr, &P.cfg.field, trig) != kOk)
+                                   nullptr, field_of<kExt>(P.cfg), trig) != kOk)
         continue;
       if (n >= kMaxPlan) break;
       const double lf = pr.l;
@@ -2231,6 +2261,7 @@ __global__ __launch_bounds__(256) void k_propagate(FindParams P, int64_t n, cons
 
 // Search-free Kalman fit: one lane per track, the hit loop in registers;
 // the per-step inputs are step-major so each step is a coalesced read.
+template <bool kExt>
 __global__ __launch_bounds__(256) void k_fit(DevCfg cfg, int64_t n, int n_steps,
                                              const int8_t *kind, const float *pos,
                                              const float *x, const float *y, const float *z,
@@ -2274,11 +2305,11 @@ __global__ __launch_bounds__(256) void k_fit(DevCfg cfg, int64_t n, int n_steps,
     fetch(min(s + 1, m - 1));
     Prop pr;
     if (propagate<true, float>(p, c, L, cfg.mkb, cfg.l_min, false, 0.f, pr, 0.f, nullptr, nullptr,
-                        &cfg.field) != kOk) {
+                               field_of<kExt>(cfg)) != kOk) {
       status = s + 1;
       break;
     }
-    material(cfg, L.kind, pr.p, pr.c, 1.f);
+    layer_material<kExt>(cfg, L.kind, pr.p, pr.c, pr.sth, pr.cth);
     Frame f;
     make_frame(pr.p, pr.c, L.kind, f);
     float u, v;
@@ -2335,7 +2366,7 @@ __device__ __forceinline__ void flip_state(T *p, T *c) {
 // (except on the first), add its scattering, take its hit (code >= 0).
 // Returns false if the surface is not reached or the hit lies in the
 // other half of the layer.
-template <typename T>
+template <bool kExt, typename T>
 __device__ __forceinline__ bool backfit_surface(const FindParams &P, const DevLayer &L,
                                                 bool first, int code, int64_t ev_base, T *p,
                                                 T *c, float &chi2) {
@@ -2345,7 +2376,7 @@ __device__ __forceinline__ bool backfit_surface(const FindParams &P, const DevLa
     flip_state(p, c);
     PropT<T> pr;
     if (propagate<true, T>(p, c, L, T(P.cfg.mkb), T(P.cfg.l_min), false, T(0), pr, T(0), nullptr,
-                           nullptr, &P.cfg.field) != kOk)
+                           nullptr, field_of<kExt>(P.cfg)) != kOk)
       return false;
 #pragma unroll
     for (int m = 0; m < 6; ++m) p[m] = pr.p[m];
@@ -2354,7 +2385,8 @@ __device__ __forceinline__ bool backfit_surface(const FindParams &P, const DevLa
     flip_state(p, c);
   }
   // on the way back the track regains the layer's loss
-  material<T>(P.cfg, L.kind, p, c, T(-1));
+  if constexpr (kExt) material<T>(P.cfg, L.kind, p, c, T(-1));
+  else add_ms(p, T(P.cfg.ms_var), c);
   if (code >= 0) {
     const HitRec h = P.byorig[ev_base + code];
     FrameT<T> f;
@@ -2390,7 +2422,8 @@ constexpr int kBfWords = 32;
 // Head, one lane per seed: as in the seed fit, the wide prior is filtered
 // through the track's first three hits in FP64 (they shrink it by ~5
 // decades, more than FP32 keeps in the covariance update).
-__global__ __launch_bounds__(256) void k_backfit_head(FindParams P, const int *seed_hits,
+template <bool kExt>
+__global__ __launch_bounds__(256, kExt ? 1 : 2) void k_backfit_head(FindParams P, const int *seed_hits,
                                                       float *tmp) {
   __shared__ DevLayer sl[kMaxLayers];
   stage_layers(P, sl);
@@ -2421,7 +2454,7 @@ __global__ __launch_bounds__(256) void k_backfit_head(FindParams P, const int *s
       int lid, code;
       if (!backfit_seq(P, hit, plan, sh, ev_base, t, lid, code)) continue;
       if (lid < 0 || lid >= P.n_layers || code >= ev_hits ||
-          !backfit_surface<double>(P, sl[lid], k == 0, code, ev_base, pd, cd, chi2)) {
+          !backfit_surface<kExt, double>(P, sl[lid], k == 0, code, ev_base, pd, cd, chi2)) {
         status = -(k + 1);
         break;
       }
@@ -2447,6 +2480,7 @@ __global__ __launch_bounds__(256) void k_backfit_head(FindParams P, const int *s
 
 // Tail, one lane per seed: the rest of the sequence in FP32; results by
 // seed id (a failed fit reports zeros).
+template <bool kExt>
 __global__ __launch_bounds__(256) void k_backfit_tail(FindParams P, const int *seed_hits,
                                                       const float *tmp, float *out_par,
                                                       float *out_cov, float *out_chi2,
@@ -2487,7 +2521,7 @@ __global__ __launch_bounds__(256) void k_backfit_tail(FindParams P, const int *s
       int lid, code;
       if (!backfit_seq(P, hit, plan, sh, ev_base, t, lid, code)) continue;
       if (lid < 0 || lid >= P.n_layers || code >= ev_hits ||
-          !backfit_surface<float>(P, sl[lid], k == 0, code, ev_base, p, c, chi2)) {
+          !backfit_surface<kExt, float>(P, sl[lid], k == 0, code, ev_base, p, c, chi2)) {
         status = -(k + 1);
         break;
       }
@@ -2533,6 +2567,7 @@ __global__ __launch_bounds__(256) void k_backfit_tail(FindParams P, const int *s
 constexpr int kSmFields = 91;
 constexpr int kSmFilt = 0, kSmPred = 27, kSmFC = 54, kSmLayer = 90;
 
+template <bool kExt>
 __global__ __launch_bounds__(256) void k_smooth_fwd(FindParams P, const int *seed_hits,
                                                     float *wk, int *n_surf) {
   __shared__ DevLayer sl[kMaxLayers];
@@ -2576,12 +2611,12 @@ __global__ __launch_bounds__(256) void k_smooth_fwd(FindParams P, const int *see
       Prop pr;
       float fc[36];
       if (propagate<true, float, true>(p, c, L, P.cfg.mkb, P.cfg.l_min, false, 0.f, pr, 0.f,
-                                       nullptr, fc, &P.cfg.field) != kOk) {
+                                       nullptr, fc, field_of<kExt>(P.cfg)) != kOk) {
         n = -1;
         break;
       }
       float j33, j35;
-      material(P.cfg, L.kind, pr.p, pr.c, 1.f, &j33, &j35);
+      layer_material<kExt>(P.cfg, L.kind, pr.p, pr.c, pr.sth, pr.cth, &j33, &j35);
       // the transport to the prediction includes the loss's Jacobian
 #pragma unroll
       for (int m = 0; m < 6; ++m) fc[18 + m] = j33 * fc[18 + m] + j35 * fc[30 + m];
@@ -2925,7 +2960,8 @@ void launch_seed(hipStream_t s, const FindParams &P, const int *src_event, const
                  int8_t *plan, float *seed_chi2, const DevRegion *regions, int n_regions,
                  const SeedCells &sc, int *cell_counts, int2 *cell_rank, int *len_counts) {
   if (P.n_seeds == 0) return;
-  hipLaunchKernelGGL(k_seed, dim3(blocks_for(P.n_seeds, kSeedBlock)), dim3(kSeedBlock), 0, s, P,
+  const auto seed = extended(P.cfg) ? k_seed<true> : k_seed<false>;
+  hipLaunchKernelGGL(seed, dim3(blocks_for(P.n_seeds, kSeedBlock)), dim3(kSeedBlock), 0, s, P,
                      src_event, src_hits, seed_event, seed_hits, seed_state, seed_ok, plan_len,
                      plan, seed_chi2, regions, n_regions, sc, cell_counts, cell_rank, len_counts);
 }
@@ -3035,25 +3071,30 @@ void launch_fit(hipStream_t s, const DevCfg &cfg, int64_t n, int n_steps, const 
                 const float *init_cov, float *out_par, float *out_cov, float *out_chi2,
                 int *out_status) {
   if (n == 0) return;
-  hipLaunchKernelGGL(k_fit, dim3(blocks_for(n, 256)), dim3(256), 0, s, cfg, n, n_steps, kind, pos,
-                     x, y, z, vu, vv, len, init_par, init_cov, out_par, out_cov, out_chi2,
+  const auto fit = extended(cfg) ? k_fit<true> : k_fit<false>;
+  hipLaunchKernelGGL(fit, dim3(blocks_for(n, 256)), dim3(256), 0, s, cfg, n, n_steps, kind, pos, x,
+                     y, z, vu, vv, len, init_par, init_cov, out_par, out_cov, out_chi2,
                      out_status);
 }
 
 void launch_backfit(hipStream_t s, const FindParams &P, const int *seed_hits, float *tmp,
                     float *out_par, float *out_cov, float *out_chi2, int *out_status) {
   if (P.n_seeds == 0) return;
-  hipLaunchKernelGGL(k_backfit_head, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P,
-                     seed_hits, tmp);
-  hipLaunchKernelGGL(k_backfit_tail, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P,
-                     seed_hits, tmp, out_par, out_cov, out_chi2, out_status);
+  const bool ext = extended(P.cfg);
+  const auto head = ext ? k_backfit_head<true> : k_backfit_head<false>;
+  const auto tail = ext ? k_backfit_tail<true> : k_backfit_tail<false>;
+  const dim3 grid(blocks_for(P.n_seeds, 256));
+  hipLaunchKernelGGL(head, grid, dim3(256), 0, s, P, seed_hits, tmp);
+  hipLaunchKernelGGL(tail, grid, dim3(256), 0, s, P, seed_hits, tmp, out_par, out_cov, out_chi2,
+                     out_status);
 }
 
 void launch_smooth(hipStream_t s, const FindParams &P, const int *seed_hits, float *wk,
                    int *n_surf, float *out_par, float *out_cov, int *out_n) {
   if (P.n_seeds == 0) return;
-  hipLaunchKernelGGL(k_smooth_fwd, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P,
-                     seed_hits, wk, n_surf);
+  const auto fwd = extended(P.cfg) ? k_smooth_fwd<true> : k_smooth_fwd<false>;
+  hipLaunchKernelGGL(fwd, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P, seed_hits, wk,
+                     n_surf);
   hipLaunchKernelGGL(k_smooth_bwd, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P, wk,
                      n_surf, out_par, out_cov, out_n);
 }
