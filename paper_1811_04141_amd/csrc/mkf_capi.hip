@@ -57,6 +57,7 @@ struct DevBuf {
 // 3.6 ms now, 2.6 ms of it the link's copy rate (57 GB/s).
 constexpr int64_t kCopyRecords = 16384;
 constexpr int kCopyThreads = 8;
+constexpr int kCopyParts = 4;  // of a call that needs one slot (at most kCopyThreads)
 
 enum Stage { kCreated = 0, kGeometry = 1, kHits = 2, kSeeds = 3, kFound = 4 };
 
@@ -989,6 +990,10 @@ mkf_status mkf_get_tracks(mkf_ctx *c, mkf_track *out, int64_t capacity, int64_t 
   if (c->stage < kFound) return fail(c, MKF_E_ORDER, "find first");
   if (n_total) *n_total = c->n_seeds;
   if (capacity < 0 || (capacity > 0 && !out)) return fail(c, MKF_E_ARG, "bad output buffer");
+  auto too_few = [&]() {
+    return fail(c, MKF_E_CAPACITY, "capacity %lld < %lld tracks", (long long)capacity,
+                (long long)c->n_seeds);
+  };
   const int64_t n = std::min(capacity, c->n_seeds);
   if (n > 0) {
     const int slots = (int)std::min<int64_t>(kCopyThreads, (n + kCopyRecords - 1) / kCopyRecords);
@@ -1002,10 +1007,29 @@ mkf_status mkf_get_tracks(mkf_ctx *c, mkf_track *out, int64_t capacity, int64_t 
                                sizeof(mkf_track) * records, hipHostMallocDefault));
       c->h_tracks_n = records;
     }
-    for (int k = 0; k < slots; ++k)
+    for (int k = 0; k < kCopyThreads; ++k)
       if (!c->ev_copy[k])
         HIP_TRY(c, hipEventCreateWithFlags(&c->ev_copy[k], hipEventDisableTiming));
     const FindParams P = params(c);
+    if (slots == 1) {
+      // few records: in up to kCopyParts parts, so that the first are copied out
+      // while the device writes the next
+      const int64_t part = std::max<int64_t>(1024, (n + kCopyParts - 1) / kCopyParts);
+      int parts = 0;
+      for (int64_t first = 0; first < n; first += part, ++parts) {
+        launch_tracks(c->stream, P, c->d_pos.as<int>(), first, std::min(part, n - first),
+                      reinterpret_cast<int *>(c->h_tracks + first));
+        HIP_TRY(c, hipGetLastError());
+        HIP_TRY(c, hipEventRecord(c->ev_copy[parts], c->stream));
+      }
+      for (int k = 0; k < parts; ++k) {
+        HIP_TRY(c, hipEventSynchronize(c->ev_copy[k]));
+        const int64_t first = k * part;
+        std::memcpy(out + first, c->h_tracks + first,
+                    sizeof(mkf_track) * (size_t)std::min(part, n - first));
+      }
+      return capacity < c->n_seeds ? too_few() : MKF_OK;
+    }
     std::atomic<int64_t> next{0};
     std::atomic<int> status{(int)hipSuccess};
     // takes chunks of seeds until none are left: the device writes a chunk's
@@ -1038,10 +1062,7 @@ mkf_status mkf_get_tracks(mkf_ctx *c, mkf_track *out, int64_t capacity, int64_t 
       return fail(c, MKF_E_HIP, "copying the tracks failed: %s",
                   hipGetErrorString((hipError_t)status.load()));
   }
-  if (capacity < c->n_seeds)
-    return fail(c, MKF_E_CAPACITY, "capacity %lld < %lld tracks", (long long)capacity,
-                (long long)c->n_seeds);
-  return MKF_OK;
+  return capacity < c->n_seeds ? too_few() : MKF_OK;
 }
 
 mkf_status mkf_propagate(mkf_ctx *c, int64_t n, const float *par, const float *cov,

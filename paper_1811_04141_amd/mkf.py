@@ -320,9 +320,15 @@ class Context:
         self._check(lib.mkf_find(self.h))
 
     def get_tracks(self, n):
-        out = np.zeros(n, TRACK_DTYPE)
+        # records beyond the seeds read as zeros: a large array's pages come
+        # zeroed and are left untouched, a small one is cleared where needed
+        # (numpy would write all of it first, 30 us for 5,000 records)
+        large = n * TRACK_DTYPE.itemsize > 16 << 20
+        out = (np.zeros if large else np.empty)(n, TRACK_DTYPE)
         tot = C.c_int64()
         self._check(lib.mkf_get_tracks(self.h, _ptr(out), n, C.byref(tot)))
+        if not large and tot.value < n:
+            out[tot.value:] = np.zeros(1, TRACK_DTYPE)
         return out
 
     def propagate(self, par, cov, layer, out_par, out_cov, out_l, out_status):

@@ -16,7 +16,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-@pytest.mark.parametrize("n", [1, CHUNK - 1, CHUNK, CHUNK + 1, 20481, 3 * CHUNK - 5,
+@pytest.mark.parametrize("n", [1, 1025, 5000, CHUNK - 1, CHUNK, CHUNK + 1, 20481, 3 * CHUNK - 5,
                                30721, 40960, 40961, 9 * CHUNK + 7])
 def test_records_in_seed_order(n):
     """An event's seeds repeated to n: every record is its seed's own, whatever
