@@ -127,7 +127,7 @@ struct mkf_ctx {
   // seeds
   int64_t n_seeds = 0;
   DevBuf d_seed_event, d_seed_hits, d_seed_state, d_seed_ok, d_plan_len, d_plan;
-  DevBuf d_seed_chi2;
+  DevBuf d_seed_chi2, d_seed_fit;
   DevBuf d_cell_counts, d_cell_start, d_cell_rank;  // the processing order's counting sort
   DevBuf d_order, d_pos, d_pstate, d_pinfo, d_pevent, d_pplan;
   DevBuf d_bf_tmp;  // backward fit: state between its FP64 and FP32 parts
@@ -178,7 +178,7 @@ struct mkf_ctx {
                      &d_bp, &d_out, &d_mlp_param, &d_mlp_m, &d_mlp_v, &d_W1p,
                      &d_W2p, &d_W3p, &d_W2T, &d_W3T, &d_mb1, &d_mb2, &d_mb3, &d_cnt, &d_radii,
                      &d_tx, &d_tt, &d_tvalid, &d_partial, &d_partial2, &d_loss, &d_grad, &d_bf_tmp, &d_sm_wk, &d_sm_n, &d_tr_cnt, &d_tr_off, &d_tr_tmp, &d_tr_kept, &d_tr_at, &d_dup_h, &d_dup_n, &d_dup_cnt, &d_dup_off,
-                     &d_dup_fill, &d_dup_list, &d_dup_tmp, &d_dup_total, &d_seed_chi2};
+                     &d_dup_fill, &d_dup_list, &d_dup_tmp, &d_dup_total, &d_seed_chi2, &d_seed_fit};
     for (DevBuf *b : all) b->release();
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -771,6 +771,7 @@ mkf_status mkf_seed(mkf_ctx *c, int64_t n_seeds, const int32_t *seed_event,
   HIP_TRY(c, c->d_plan_len.ensure(4 * N));
   HIP_TRY(c, c->d_plan.ensure(kMaxPlan * N));
   HIP_TRY(c, c->d_seed_chi2.ensure(4 * N));
+  HIP_TRY(c, c->d_seed_fit.ensure(sizeof(double) * kSeedFit * N));
   HIP_TRY(c, c->d_cell_counts.ensure(sizeof(int) * (size_t)(n_cells + n_len)));
   HIP_TRY(c, c->d_cell_start.ensure(sizeof(int) * (size_t)(n_cells + 1)));
   HIP_TRY(c, c->d_cell_rank.ensure(sizeof(int2) * N));
@@ -805,6 +806,7 @@ mkf_status mkf_seed(mkf_ctx *c, int64_t n_seeds, const int32_t *seed_event,
   launch_seed(c->stream, P, src_event, src_hits, c->d_seed_event.as<int>(),
               c->d_seed_hits.as<int>(), c->d_seed_state.as<float>(), c->d_seed_ok.as<int>(),
               c->d_plan_len.as<int>(), c->d_plan.as<int8_t>(), c->d_seed_chi2.as<float>(),
+              c->d_seed_fit.as<double>(),
               c->n_regions > 0 ? c->d_regions.as<DevRegion>() : nullptr, c->n_regions, cells,
               c->d_cell_counts.as<int>(), c->d_cell_rank.as<int2>(), len_counts);
   HIP_TRY(c, hipGetLastError());

@@ -1227,14 +1227,16 @@ __global__ __launch_bounds__(256) void k_tracks(FindParams P, const int *pos_of,
 // holds the seed's pseudorapidity, less the seed layers; without, it is built
 // per seed: every other layer the seed helix crosses inside its widened
 // extent, by increasing path length.
-
 //
-// One wavefront per block and one lane per seed; the plan under construction
-// (path lengths and layers) is in LDS.  Bound by the FP64 arithmetic of the
-// fit and of some 25 crossings.  500,000 seeds: 430 us (535 us with the plan in
-// global scratch memory and the sines and cosines of the state taken anew for
-// every layer); 5,000 seeds: 50 us (57 us in blocks of 256).
+// Two kernels.  k_seed fits, one lane per seed, one wavefront per block; its 21
+// covariances in FP64 leave it one wave per SIMD, bound by the latency of the
+// FP64 chain.  k_seed_plan takes the crossings, four or eight lanes per seed, each
+// with its share of the layers: few registers, many waves, and a chain of a few
+// crossings instead of 25.  The whole of the seeding kernels: 200 seeds 23 us, 5,000
+// 34 us, against 27 and 46 in one kernel with one lane per seed; 500,000 seeds 129 us
+// of fit and 201 us of plans against 378.
 constexpr int kSeedBlock = 64;
+constexpr int kFewPlans = 32768;  // seeds up to which a plan has eight lanes
 
 __global__ __launch_bounds__(256) void k_validate_seeds(FindParams P, const int *seed_event,
                                                         const int *seed_hits, int *bad) {
@@ -1255,25 +1257,17 @@ __global__ __launch_bounds__(256) void k_validate_seeds(FindParams P, const int 
 template <bool kExt>
 __global__ __launch_bounds__(kSeedBlock) void k_seed(
     FindParams P, const int *src_event, const int *src_hits, int *seed_event, int *seed_hits,
-    float *seed_state, int *seed_ok, int *plan_len, int8_t *plan, float *seed_chi2,
-    const DevRegion *regions, int n_regions, SeedCells cells, int *cell_counts, int2 *cell_rank,
-    int *len_counts) {
+    float *seed_state, int *seed_ok, float *seed_chi2, double *fit) {
   __shared__ DevLayer sl[kMaxLayers];
-  __shared__ double s_l[kMaxPlan][kSeedBlock];   // the plan's path lengths
-  __shared__ int8_t s_plan[kMaxPlan][kSeedBlock];
-  __shared__ int s_len[kLenWords];
   stage_layers(P, sl);
-  for (int k = threadIdx.x; k < kLenWords; k += blockDim.x) s_len[k] = 0;
   __syncthreads();
-  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool valid = i0 < P.n_seeds;
-  const int64_t i = valid ? i0 : P.n_seeds - 1;  // (idle lanes repeat the last seed, unwritten)
-  const int me = threadIdx.x;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= P.n_seeds) return;
   const int ev = src_event[i];
   const int64_t e0 = P.ev_off[ev];
   int sh[3];
   for (int k = 0; k < 3; ++k) sh[k] = src_hits[3 * i + k];
-  if (valid && src_event != seed_event) {
+  if (src_event != seed_event) {
     seed_event[i] = ev;
     for (int k = 0; k < 3; ++k) seed_hits[3 * i + k] = sh[k];
   }
@@ -1292,9 +1286,8 @@ __global__ __launch_bounds__(kSeedBlock) void k_seed(
     hvv[k] = var.y;
     hl[k] = h.layer;
   }
-  const double mkb = P.cfg.mkb, l_min = P.cfg.l_min, edge = P.cfg.edge_margin;
+  const double mkb = P.cfg.mkb, l_min = P.cfg.l_min;
   int ok = 0;
-  int n = 0;
   double p[6], c[21], chi2 = 0.0;
   do {
     const double ax = hx[1] - hx[0], ay = hy[1] - hy[0];
@@ -1351,44 +1344,9 @@ __global__ __launch_bounds__(kSeedBlock) void k_seed(
     }
     if (!good) break;
     ok = 1;
-    if (n_regions > 0) {
-      const double eta = -log(tan(0.5 * p[5]));
-      int r = 0;
-      while (r < n_regions && !(eta >= regions[r].eta_lo && eta < regions[r].eta_hi)) ++r;
-      if (r < n_regions) {
-        const DevRegion &g = regions[r];
-        for (int k = 0; k < g.n && n < kMaxPlan; ++k) {
-          const int L = g.layers[k];
-          if (L == hl[0] || L == hl[1] || L == hl[2]) continue;
-          s_plan[n++][me] = (int8_t)L;
-        }
-      }
-      break;
-    }
-    // plan: insertion by path length (ties by layer id)
-    double trig[4];
-    sincos_t(p[4], &trig[0], &trig[1]);
-    sincos_t(p[5], &trig[2], &trig[3]);
-    for (int L = 0; L < P.n_layers; ++L) {
-      if (L == hl[0] || L == hl[1] || L == hl[2]) continue;
-      PropT<double> pr;
-      if (propagate<false, double>(p, nullptr, sl[L], mkb, l_min, true, edge, pr, 0.0, nullptr,
-                                   nullptr, field_of<kExt>(P.cfg), trig) != kOk)
-        continue;
-      if (n >= kMaxPlan) break;
-      const double lf = pr.l;
-      int j = n;
-      while (j > 0 && s_l[j - 1][me] > lf) {
-        s_l[j][me] = s_l[j - 1][me];
-        s_plan[j][me] = s_plan[j - 1][me];
-        --j;
-      }
-      s_l[j][me] = lf;
-      s_plan[j][me] = (int8_t)L;
-      ++n;
-    }
   } while (false);
-  n = ok ? n : 0;
+  seed_ok[i] = ok;
+  seed_chi2[i] = ok ? (float)chi2 : 0.f;
   float w[kSeedWords];
 #pragma unroll
   for (int k = 0; k < 6; ++k) w[k] = ok ? (float)p[k] : 0.f;
@@ -1397,33 +1355,119 @@ __global__ __launch_bounds__(kSeedBlock) void k_seed(
   // the row's last word: the index of the event's first hit (below 2^31),
   // read with the state so that the find need not look it up
   w[27] = __int_as_float((int)e0);
-  if (valid) {
-    seed_ok[i] = ok;
-    seed_chi2[i] = ok ? (float)chi2 : 0.f;
-    plan_len[i] = n;
-    float4 *row = reinterpret_cast<float4 *>(seed_state + (size_t)i * kSeedWords);
+  float4 *row = reinterpret_cast<float4 *>(seed_state + (size_t)i * kSeedWords);
 #pragma unroll
-    for (int k = 0; k < kSeedWords / 4; ++k)
-      row[k] = make_float4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-    int *pw = reinterpret_cast<int *>(plan + (size_t)i * kMaxPlan);
-    for (int k = 0; k < kMaxPlan / 4; ++k) {
-      unsigned v = 0;
-      for (int b = 0; b < 4; ++b)
-        v |= (4 * k + b < n ? (unsigned)(uint8_t)s_plan[4 * k + b][me] : 0xFFu) << (8 * b);
-      pw[k] = (int)v;
+  for (int k = 0; k < kSeedWords / 4; ++k)
+    row[k] = make_float4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
+  if (ok) {  // for the plan: the state, its sines and cosines, the seed's layers
+    double f[kSeedFit];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) f[k] = p[k];
+    sincos_t(p[4], &f[6], &f[7]);
+    sincos_t(p[5], &f[8], &f[9]);
+    f[10] = (double)(hl[0] | hl[1] << 8 | hl[2] << 16);
+    f[11] = 0.0;
+    double2 *dst = reinterpret_cast<double2 *>(fit + (size_t)i * kSeedFit);
+#pragma unroll
+    for (int k = 0; k < kSeedFit / 2; ++k) dst[k] = make_double2(f[2 * k], f[2 * k + 1]);
+  }
+}
+
+// Layer plans and places in the processing order, kLanes lanes per seed.
+template <bool kExt, int kLanes>
+__global__ __launch_bounds__(256) void k_seed_plan(
+    FindParams P, const double *fit, int *plan_len, int8_t *plan, const DevRegion *regions,
+    int n_regions, SeedCells cells, int *cell_counts, int2 *cell_rank, int *len_counts) {
+  constexpr int kPlanSeeds = 256 / kLanes;
+  __shared__ DevLayer sl[kMaxLayers];
+  __shared__ double s_path[kPlanSeeds][kMaxLayers + 1];  // path to every layer, < 0: none
+  __shared__ double s_l[kPlanSeeds][kMaxPlan + 1];       // the plan's path lengths
+  __shared__ __attribute__((aligned(4))) uint8_t s_plan[kPlanSeeds][kMaxPlan];
+  __shared__ int s_len[kLenWords];
+  stage_layers(P, sl);
+  for (int k = threadIdx.x; k < kLenWords; k += blockDim.x) s_len[k] = 0;
+  __syncthreads();
+  const int g = threadIdx.x / kLanes, sub = threadIdx.x % kLanes;
+  const int64_t i0 = (int64_t)blockIdx.x * kPlanSeeds + g;
+  const bool valid = i0 < P.n_seeds;
+  const int64_t i = valid ? i0 : P.n_seeds - 1;  // (idle lanes repeat the last seed, unwritten)
+  const bool ok = P.seed_ok[i] != 0;
+  double p[6], trig[4];
+  int hl[3] = {};
+  if (ok) {
+    const double *f = fit + (size_t)i * kSeedFit;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) p[k] = f[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) trig[k] = f[6 + k];
+    const int h = (int)f[10];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) hl[k] = (h >> (8 * k)) & 0xFF;
+    if (n_regions == 0) {
+      const double mkb = P.cfg.mkb, l_min = P.cfg.l_min, edge = P.cfg.edge_margin;
+      for (int L = sub; L < P.n_layers; L += kLanes) {
+        double l = -1.0;
+        if (L != hl[0] && L != hl[1] && L != hl[2]) {
+          PropT<double> pr;
+          if (propagate<false, double>(p, nullptr, sl[L], mkb, l_min, true, edge, pr, 0.0,
+                                       nullptr, nullptr, field_of<kExt>(P.cfg), trig) == kOk)
+            l = pr.l;
+        }
+        s_path[g][L] = l;
+      }
     }
+  }
+  int *plan_w = reinterpret_cast<int *>(s_plan[g]);
+  for (int k = sub; k < kMaxPlan / 4; k += kLanes) plan_w[k] = -1;
+  wave_sync();
+  if (sub == 0 && valid) {
+    int n = 0;
+    if (ok && n_regions > 0) {
+      const double eta = -log(tan(0.5 * p[5]));
+      int r = 0;
+      while (r < n_regions && !(eta >= regions[r].eta_lo && eta < regions[r].eta_hi)) ++r;
+      if (r < n_regions) {
+        const DevRegion &rg = regions[r];
+        for (int k = 0; k < rg.n && n < kMaxPlan; ++k) {
+          const int L = rg.layers[k];
+          if (L == hl[0] || L == hl[1] || L == hl[2]) continue;
+          s_plan[g][n++] = (uint8_t)L;
+        }
+      }
+    } else if (ok) {
+      // insertion by path length (ties by layer id)
+      for (int L = 0; L < P.n_layers && n < kMaxPlan; ++L) {
+        const double lf = s_path[g][L];
+        if (lf < 0.0) continue;
+        int j = n;
+        while (j > 0 && s_l[g][j - 1] > lf) {
+          s_l[g][j] = s_l[g][j - 1];
+          s_plan[g][j] = s_plan[g][j - 1];
+          --j;
+        }
+        s_l[g][j] = lf;
+        s_plan[g][j] = (uint8_t)L;
+        ++n;
+      }
+    }
+    plan_len[i] = n;
     // the processing order's cell (a state that is not a number: cell 0)
-    const float tc = w[5] * 8.f, pc = (w[4] + kPi) * (kPhiCells / kTwoPi);
+    const float theta = ok ? (float)p[5] : 0.f, phi = ok ? (float)p[4] : 0.f;
+    const float tc = theta * 8.f, pc = (phi + kPi) * (kPhiCells / kTwoPi);
     const int ti = tc > 0.f ? min((int)fminf(tc, 1e6f), kThetaCells - 1) : 0;
     const int pi = pc > 0.f ? min((int)fminf(pc, 1e6f), kPhiCells - 1) : 0;
     const int dir = ti * kPhiCells + pi;
-    const int64_t grp = ev >> cells.event_shift, len = kMaxPlan - n;
+    const int64_t grp = P.seed_event[i] >> cells.event_shift, len = kMaxPlan - n;
     const int64_t cell = (cells.by_length ? len * cells.n_groups + grp
                                           : grp * kPlanLens + len) * kDirCells + dir;
     cell_rank[i] = make_int2((int)cell, atomicAdd(&cell_counts[cell], 1));
     atomicAdd(&s_len[n], 1);
     if (ok) atomicAdd(&s_len[kPlanLens], 1);
   }
+  wave_sync();
+  if (valid)
+    for (int k = sub; k < kMaxPlan / 4; k += kLanes)
+      reinterpret_cast<int *>(plan + (size_t)i * kMaxPlan)[k] = plan_w[k];
   __syncthreads();
   for (int k = threadIdx.x; k < kLenWords; k += blockDim.x)
     if (s_len[k]) atomicAdd(&len_counts[blockIdx.x % kLenSlots * kLenWords + k], s_len[k]);
@@ -2957,13 +3001,24 @@ void launch_validate_seeds(hipStream_t s, const FindParams &P, const int *seed_e
 
 void launch_seed(hipStream_t s, const FindParams &P, const int *src_event, const int *src_hits,
                  int *seed_event, int *seed_hits, float *seed_state, int *seed_ok, int *plan_len,
-                 int8_t *plan, float *seed_chi2, const DevRegion *regions, int n_regions,
-                 const SeedCells &sc, int *cell_counts, int2 *cell_rank, int *len_counts) {
+                 int8_t *plan, float *seed_chi2, double *fit, const DevRegion *regions,
+                 int n_regions, const SeedCells &sc, int *cell_counts, int2 *cell_rank,
+                 int *len_counts) {
   if (P.n_seeds == 0) return;
-  const auto seed = extended(P.cfg) ? k_seed<true> : k_seed<false>;
+  const bool ext = extended(P.cfg);
+  const auto seed = ext ? k_seed<true> : k_seed<false>;
   hipLaunchKernelGGL(seed, dim3(blocks_for(P.n_seeds, kSeedBlock)), dim3(kSeedBlock), 0, s, P,
-                     src_event, src_hits, seed_event, seed_hits, seed_state, seed_ok, plan_len,
-                     plan, seed_chi2, regions, n_regions, sc, cell_counts, cell_rank, len_counts);
+                     src_event, src_hits, seed_event, seed_hits, seed_state, seed_ok, seed_chi2,
+                     fit);
+  // Eight lanes per seed shorten the chain, four do less twice over: at 500,000 seeds the plans
+  // take 286 us with eight and 201 with four, at 108,000 91 and 78; 5,000 seeds leave most of
+  // the chip idle with either, and the shorter chain counts.
+  const bool few = P.n_seeds <= kFewPlans;
+  const int lanes = few ? 8 : 4;
+  const auto plans = few ? (ext ? k_seed_plan<true, 8> : k_seed_plan<false, 8>)
+                         : (ext ? k_seed_plan<true, 4> : k_seed_plan<false, 4>);
+  hipLaunchKernelGGL(plans, dim3(blocks_for(P.n_seeds, 256 / lanes)), dim3(256), 0, s, P, fit,
+                     plan_len, plan, regions, n_regions, sc, cell_counts, cell_rank, len_counts);
 }
 
 void launch_place_seeds(hipStream_t s, const FindParams &P, const int2 *cell_rank,

@@ -204,11 +204,14 @@ constexpr int kLenSlots = 64, kLenWords = kPlanLens + 1;
 void launch_validate_seeds(hipStream_t s, const FindParams &P, const int *seed_event,
                            const int *seed_hits, int *bad);
 // fits the seeds given by src_event, src_hits (copied to seed_event, seed_hits
-// where those are other arrays) and counts them by cell and by plan length
+// where those are other arrays), builds their plans and counts them by cell and
+// by plan length; fit holds kSeedFit words per seed between the two
+constexpr int kSeedFit = 12;
 void launch_seed(hipStream_t s, const FindParams &P, const int *src_event, const int *src_hits,
                  int *seed_event, int *seed_hits, float *seed_state, int *seed_ok, int *plan_len,
-                 int8_t *plan, float *seed_chi2, const DevRegion *regions, int n_regions,
-                 const SeedCells &sc, int *cell_counts, int2 *cell_rank, int *len_counts);
+                 int8_t *plan, float *seed_chi2, double *fit, const DevRegion *regions,
+                 int n_regions, const SeedCells &sc, int *cell_counts, int2 *cell_rank,
+                 int *len_counts);
 // the seeds' results into processing order
 void launch_place_seeds(hipStream_t s, const FindParams &P, const int2 *cell_rank,
                         const int *cell_start, int *order, int *pos_of, float *pstate, int *pinfo,
