@@ -827,11 +827,19 @@ __global__ __launch_bounds__(256, kMat ? 1 : 4) void k_find_step(FindParams P, i
   }
 }
 
+// Block of the kernels that take one lane per track through its surfaces: one
+// wavefront.  Their calls are often smaller than the chip (20,000 tracks are 316
+// wavefronts for 1,024 SIMDs), and blocks of four put them on a third of the
+// CUs.  Against blocks of 256, 20,000 tracks: forward smoothing 59 to 54 us,
+// backward 100 to 82, results 29 to 26; 500,000 tracks: the backward fit's
+// head 148 to 140, its tail 235 to 234.
+constexpr int kTrackBlock = 64;
+
 // Best of the final and the retired candidates of each seed (more hits,
 // then smaller chi2) and the count of candidate-layer steps (1 for the seed
 // at step 0, then every kept extension carried into the next step).  One
 // lane per seed.
-__global__ __launch_bounds__(256) void k_finalize(FindParams P) {
+__global__ __launch_bounds__(kTrackBlock) void k_finalize(FindParams P) {
   __shared__ unsigned long long block_steps;
   if (threadIdx.x == 0) block_steps = 0;
   __syncthreads();
@@ -2467,7 +2475,7 @@ constexpr int kBfWords = 32;
 // through the track's first three hits in FP64 (they shrink it by ~5
 // decades, more than FP32 keeps in the covariance update).
 template <bool kExt>
-__global__ __launch_bounds__(256, kExt ? 1 : 2) void k_backfit_head(FindParams P, const int *seed_hits,
+__global__ __launch_bounds__(kTrackBlock, kExt ? 1 : 2) void k_backfit_head(FindParams P, const int *seed_hits,
                                                       float *tmp) {
   __shared__ DevLayer sl[kMaxLayers];
   stage_layers(P, sl);
@@ -2525,7 +2533,7 @@ __global__ __launch_bounds__(256, kExt ? 1 : 2) void k_backfit_head(FindParams P
 // Tail, one lane per seed: the rest of the sequence in FP32; results by
 // seed id (a failed fit reports zeros).
 template <bool kExt>
-__global__ __launch_bounds__(256) void k_backfit_tail(FindParams P, const int *seed_hits,
+__global__ __launch_bounds__(kTrackBlock) void k_backfit_tail(FindParams P, const int *seed_hits,
                                                       const float *tmp, float *out_par,
                                                       float *out_cov, float *out_chi2,
                                                       int *out_status) {
@@ -2612,7 +2620,7 @@ constexpr int kSmFields = 91;
 constexpr int kSmFilt = 0, kSmPred = 27, kSmFC = 54, kSmLayer = 90;
 
 template <bool kExt>
-__global__ __launch_bounds__(256) void k_smooth_fwd(FindParams P, const int *seed_hits,
+__global__ __launch_bounds__(kTrackBlock) void k_smooth_fwd(FindParams P, const int *seed_hits,
                                                     float *wk, int *n_surf) {
   __shared__ DevLayer sl[kMaxLayers];
   stage_layers(P, sl);
@@ -2746,29 +2754,49 @@ __device__ __forceinline__ void sandwich5(const FreeCoords &J, const float *M, f
   }
 }
 
-// solve (L L^T) x = b in place, L lower-triangular 5x5 packed by rows
-__device__ __forceinline__ void chol_solve5(const float *Lp, float *b) {
+// a / d, inv = 1 / d rounded, d the square root of a positive float (so inv is
+// normal, or zero where d is infinite): the quotient corrected once by its exact
+// remainder, which rounds as the division does, in 5 instructions instead of
+// the 10 of a general one.  Where the remainder overflows (an infinite
+// operand or quotient) the product is already what the division gives.  Of
+// 3e8 pairs over the whole range of a and d the results differ from the
+// division's only where the remainder is subnormal (|a| < 1e-30), by one ulp.
+__device__ __forceinline__ float over(float a, float d, float inv) {
+  const float q = a * inv;
+  const float r = fmaf(-q, d, a);
+  return fabsf(r) < __builtin_inff() ? fmaf(r, inv, q) : q;
+}
+
+// solve (L L^T) x = b in place, L lower-triangular 5x5 packed by rows, inv: the
+// reciprocals of its diagonal
+__device__ __forceinline__ void chol_solve5(const float *Lp, const float *inv, float *b) {
   float y[5];
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
     float a = b[i];
 #pragma unroll
     for (int k = 0; k < i; ++k) a = fmaf(-Lp[i * (i + 1) / 2 + k], y[k], a);
-    y[i] = a / Lp[i * (i + 1) / 2 + i];
+    y[i] = over(a, Lp[i * (i + 1) / 2 + i], inv[i]);
   }
 #pragma unroll
   for (int i = 4; i >= 0; --i) {
     float a = y[i];
 #pragma unroll
     for (int k = i + 1; k < 5; ++k) a = fmaf(-Lp[k * (k + 1) / 2 + i], b[k], a);
-    b[i] = a / Lp[i * (i + 1) / 2 + i];
+    b[i] = over(a, Lp[i * (i + 1) / 2 + i], inv[i]);
   }
 }
 
 // Backward pass, FP32: the 5 x 5 systems are well conditioned once scaled
 // by their diagonal (condition numbers of the correlation matrices up to
-// ~500 on the benchmark's tracks), which a Cholesky solve respects.
-__global__ __launch_bounds__(256) void k_smooth_bwd(FindParams P, const float *wk,
+// ~500 on the benchmark's tracks), which a Cholesky solve respects.  One
+// lane per track: 20,000 tracks are 316 wavefronts, each bound by the issue of its
+// own chain, of which 80 divisions per surface were the largest part.  20,000
+// tracks of 14 surfaces 100 us with general divisions and blocks of 256, 82 with
+// blocks of 64, 67 with the quotients of over() as well.  Eight lanes per track
+// with the matrices in LDS took 83, four 113: the factor is then taken by every
+// lane, and each surface waits for LDS four times.
+__global__ __launch_bounds__(kTrackBlock) void k_smooth_bwd(FindParams P, const float *wk,
                                                     const int *n_surf, float *out_par,
                                                     float *out_cov, int *out_n) {
   const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2790,11 +2818,19 @@ __global__ __launch_bounds__(256) void k_smooth_bwd(FindParams P, const float *w
 #pragma unroll
     for (int m = 0; m < 21; ++m) oc[(n - 1) * 21 + m] = Cs[m];
     for (int k = n - 2; k >= 0; --k) {
+      // the step's 91 words in one group of loads
+      float pred[27], fc[36], filt[27];
+      const int lid = __float_as_int(at(k + 1, kSmLayer));
+#pragma unroll
+      for (int m = 0; m < 27; ++m) pred[m] = at(k + 1, kSmPred + m);
+#pragma unroll
+      for (int m = 0; m < 36; ++m) fc[m] = at(k + 1, kSmFC + m);
+#pragma unroll
+      for (int m = 0; m < 27; ++m) filt[m] = at(k, kSmFilt + m);
       // surface k+1: its free coordinates at the predicted point
       float xp[6];
 #pragma unroll
-      for (int m = 0; m < 6; ++m) xp[m] = at(k + 1, kSmPred + m);
-      const int lid = __float_as_int(at(k + 1, kSmLayer));
+      for (int m = 0; m < 6; ++m) xp[m] = pred[m];
       FreeCoords J;
       if (P.layers[lid].kind == 0) {
         const float ir = rsqrtf(fmaf(xp[0], xp[0], xp[1] * xp[1]));
@@ -2803,11 +2839,11 @@ __global__ __launch_bounds__(256) void k_smooth_bwd(FindParams P, const float *w
         J = FreeCoords{1.f, 0.f, 0.f, 1.f, 0.f};
       }
       // Sr = J Cp J^T, then dPr = J (Cs - Cp) J^T
-      float Sr[15], dPr[15];
+      float Sr[15], dPr[15], inv[5];
       {
         float Cp[21];
 #pragma unroll
-        for (int m = 0; m < 21; ++m) Cp[m] = at(k + 1, kSmPred + 6 + m);
+        for (int m = 0; m < 21; ++m) Cp[m] = pred[6 + m];
         sandwich5(J, Cp, Sr);
 #pragma unroll
         for (int m = 0; m < 21; ++m) Cs[m] -= Cp[m];
@@ -2825,8 +2861,9 @@ __global__ __launch_bounds__(256) void k_smooth_bwd(FindParams P, const float *w
           if (i == j) {
             pd = pd && a > 0.f;
             Sr[i * (i + 1) / 2 + i] = sqrtf(a > 0.f ? a : 1.f);
+            inv[i] = 1.f / Sr[i * (i + 1) / 2 + i];
           } else {
-            Sr[i * (i + 1) / 2 + j] = a / Sr[j * (j + 1) / 2 + j];
+            Sr[i * (i + 1) / 2 + j] = over(a, Sr[j * (j + 1) / 2 + j], inv[j]);
           }
         }
       }
@@ -2840,7 +2877,7 @@ __global__ __launch_bounds__(256) void k_smooth_bwd(FindParams P, const float *w
       for (int m = 0; m < 6; ++m) d[m] = xs[m] - xp[m];
       d[4] = wrap_phi(d[4]);
       J.apply(d, u);
-      chol_solve5(Sr, u);
+      chol_solve5(Sr, inv, u);
       // M = J F C (5 x 6), one column at a time: xs(k) = x(k) + M^T u and
       // W = Sr^-1 M
       float W[5][6];
@@ -2848,13 +2885,13 @@ __global__ __launch_bounds__(256) void k_smooth_bwd(FindParams P, const float *w
       for (int j = 0; j < 6; ++j) {
         float col[6], w[5];
 #pragma unroll
-        for (int i = 0; i < 6; ++i) col[i] = at(k + 1, kSmFC + i * 6 + j);
+        for (int i = 0; i < 6; ++i) col[i] = fc[i * 6 + j];
         J.apply(col, w);
-        float a = at(k, kSmFilt + j);
+        float a = filt[j];
 #pragma unroll
         for (int q = 0; q < 5; ++q) a = fmaf(w[q], u[q], a);
         xs[j] = a;
-        chol_solve5(Sr, w);
+        chol_solve5(Sr, inv, w);
 #pragma unroll
         for (int q = 0; q < 5; ++q) W[q][j] = w[q];
       }
@@ -2873,7 +2910,7 @@ __global__ __launch_bounds__(256) void k_smooth_bwd(FindParams P, const float *w
         }
 #pragma unroll
         for (int j = i; j < 6; ++j) {
-          float v = at(k, kSmFilt + 6 + tri(i, j));
+          float v = filt[6 + tri(i, j)];
 #pragma unroll
           for (int a = 0; a < 5; ++a) v = fmaf(t[a], W[a][j], v);
           Cs[tri(i, j)] = v;
@@ -3098,7 +3135,7 @@ void launch_find_persistent(hipStream_t s, const FindParams &P, int grid_blocks,
 
 void launch_finalize(hipStream_t s, const FindParams &P) {
   if (P.n_seeds == 0) return;
-  hipLaunchKernelGGL(k_finalize, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P);
+  hipLaunchKernelGGL(k_finalize, dim3(blocks_for(P.n_seeds, kTrackBlock)), dim3(kTrackBlock), 0, s, P);
 }
 void launch_check_results(hipStream_t s, const FindParams &P) {
   if (P.n_seeds == 0) return;
@@ -3138,9 +3175,9 @@ void launch_backfit(hipStream_t s, const FindParams &P, const int *seed_hits, fl
   const bool ext = extended(P.cfg);
   const auto head = ext ? k_backfit_head<true> : k_backfit_head<false>;
   const auto tail = ext ? k_backfit_tail<true> : k_backfit_tail<false>;
-  const dim3 grid(blocks_for(P.n_seeds, 256));
-  hipLaunchKernelGGL(head, grid, dim3(256), 0, s, P, seed_hits, tmp);
-  hipLaunchKernelGGL(tail, grid, dim3(256), 0, s, P, seed_hits, tmp, out_par, out_cov, out_chi2,
+  const dim3 grid(blocks_for(P.n_seeds, kTrackBlock));
+  hipLaunchKernelGGL(head, grid, dim3(kTrackBlock), 0, s, P, seed_hits, tmp);
+  hipLaunchKernelGGL(tail, grid, dim3(kTrackBlock), 0, s, P, seed_hits, tmp, out_par, out_cov, out_chi2,
                      out_status);
 }
 
@@ -3148,9 +3185,9 @@ void launch_smooth(hipStream_t s, const FindParams &P, const int *seed_hits, flo
                    int *n_surf, float *out_par, float *out_cov, int *out_n) {
   if (P.n_seeds == 0) return;
   const auto fwd = extended(P.cfg) ? k_smooth_fwd<true> : k_smooth_fwd<false>;
-  hipLaunchKernelGGL(fwd, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P, seed_hits, wk,
+  hipLaunchKernelGGL(fwd, dim3(blocks_for(P.n_seeds, kTrackBlock)), dim3(kTrackBlock), 0, s, P, seed_hits, wk,
                      n_surf);
-  hipLaunchKernelGGL(k_smooth_bwd, dim3(blocks_for(P.n_seeds, 256)), dim3(256), 0, s, P, wk,
+  hipLaunchKernelGGL(k_smooth_bwd, dim3(blocks_for(P.n_seeds, kTrackBlock)), dim3(kTrackBlock), 0, s, P, wk,
                      n_surf, out_par, out_cov, out_n);
 }
 

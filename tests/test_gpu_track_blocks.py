@@ -1,0 +1,42 @@
+"""The kernels that take one lane per track in blocks of one wavefront: results,
+smoothed states and refits do not depend on how many tracks share the call."""
+import numpy as np
+import pytest
+
+from synth import barrel_endcap, generate
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+def test_tracks_do_not_depend_on_the_block_they_fall_in(flags):
+    from paper_1811_04141_amd import mkf
+    w = barrel_endcap(1, 300)
+    b = generate(w)
+    c = mkf.Context(w.find, flags=flags)
+    c.load_geometry(w.layers)
+    c.load_hits(b.ev_off, dev(b.x), dev(b.y), dev(b.z), dev(b.var_u), dev(b.var_v), dev(b.layer))
+
+    def run(n):
+        c.seed(dev(b.seed_event[:n]), dev(b.seed_hits[:n]))
+        c.find()
+        k = mkf.MAX_PLAN + 1
+        z = [torch.zeros(s, device="cuda") for s in ((n, k, 6), (n, k, 21), (n, 6), (n, 21), (n,))]
+        i = [torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(2)]
+        c.smooth(z[0], z[1], i[0])
+        c.backward_fit(z[2], z[3], z[4], i[1])
+        torch.cuda.synchronize()
+        return [c.get_tracks(n)] + [t.cpu().numpy() for t in z + i]
+
+    ref = run(b.seed_hits.shape[0])
+    assert (ref[6] > 3).any() and (ref[7] == 1).any()
+    for n in (1, 63, 64, 65, 129):
+        for got, want in zip(run(n), ref):
+            assert got.tobytes() == np.ascontiguousarray(want[:n]).tobytes(), n
+    c.close()
