@@ -205,9 +205,6 @@ struct GlobalRec {
   __device__ void put_bp(int step, int slot, int v) const {
     P->bp[((size_t)step * (size_t)P->n_seeds + pos) * P->slots + slot] = v;
   }
-  __device__ int get_bp(int step, int slot) const {
-    return P->bp[((size_t)step * (size_t)P->n_seeds + pos) * P->slots + slot];
-  }
   __device__ void put_fin(const Cand &cd) const {
     const size_t N = (size_t)P->n_seeds;
 #pragma unroll
@@ -711,10 +708,8 @@ __device__ __forceinline__ void store_cand(const FindParams &P, size_t idx, cons
 // The chosen candidate of a seed: state and counts, and its hit history
 // followed back through the per-step back-pointers from (best_step,
 // best_slot).  Plan steps after the candidate stopped read MKF_HIT_NONE.
-template <class Rec>
-__device__ __forceinline__ void write_result(const FindParams &P, int64_t pos, const Rec &rec,
-                                             const float *p, const float *c, float chi2, int nh,
-                                             int nm, int best_step, int best_slot, int plen) {
+__device__ __forceinline__ int *write_state(const FindParams &P, int64_t pos, const float *p,
+                                           const float *c, float chi2, int nh, int nm) {
   float *out = P.out + (size_t)pos * kOutWords;
   float w[kOutHit];
 #pragma unroll
@@ -728,7 +723,14 @@ __device__ __forceinline__ void write_result(const FindParams &P, int64_t pos, c
 #pragma unroll
   for (int k = 0; k < kOutHit / 4; ++k)
     reinterpret_cast<float4 *>(out)[k] = make_float4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-  int *hit = reinterpret_cast<int *>(out + kOutHit);
+  return reinterpret_cast<int *>(out + kOutHit);
+}
+
+template <class Rec>
+__device__ __forceinline__ void write_result(const FindParams &P, int64_t pos, const Rec &rec,
+                                             const float *p, const float *c, float chi2, int nh,
+                                             int nm, int best_step, int best_slot, int plen) {
+  int *hit = write_state(P, pos, p, c, chi2, nh, nm);
   for (int s = plen - 1; s > best_step; --s) hit[s] = MKF_HIT_NONE;
   int sl = best_slot;
   for (int s = best_step; s >= 0; --s) {
@@ -839,7 +841,14 @@ constexpr int kTrackBlock = 64;
 // then smaller chi2) and the count of candidate-layer steps (1 for the seed
 // at step 0, then every kept extension carried into the next step).  One
 // lane per seed.
+//
+// The back-pointer rows of eight steps are requested at once, counted, and
+// followed in registers: read one by one, 78 words for the count and then a
+// chain of a load per step were waited for in turn (20,000 seeds of 14 steps: 26
+// us, now 17).
+template <int G>
 __global__ __launch_bounds__(kTrackBlock) void k_finalize(FindParams P) {
+  constexpr int kRows = 8;
   __shared__ unsigned long long block_steps;
   if (threadIdx.x == 0) block_steps = 0;
   __syncthreads();
@@ -849,15 +858,12 @@ __global__ __launch_bounds__(kTrackBlock) void k_finalize(FindParams P) {
     const int plen = info & 0xFF;
     const bool ok = (info >> 8) & 1;
     const size_t N = (size_t)P.n_seeds;
-    const int G = P.slots;
     const size_t NS = N * G;
     int cnt = (ok && plen > 0) ? 1 : 0;
-    for (int s = 0; s + 1 < plen; ++s)
-      for (int j = 0; j < G; ++j) cnt += P.bp[((size_t)s * N + pos) * G + j] >= 0;
-    if (cnt) atomicAdd(&block_steps, (unsigned long long)cnt);
     u64 m = kKeyMax;
     int best = 0;
     if (ok)
+#pragma unroll
       for (int j = 0; j < G; ++j) {
         const int meta = __float_as_int(P.cand[28 * NS + pos * G + j]);
         if (!((meta >> 16) & 1)) continue;
@@ -868,16 +874,63 @@ __global__ __launch_bounds__(kTrackBlock) void k_finalize(FindParams P) {
         }
       }
     const u64 fin = ok ? P.fin_key[pos] : kKeyMax;
-    const GlobalRec rec{&P, pos};
-    if (m != kKeyMax && m < fin) {
+    const bool live = m != kKeyMax && m < fin;
+    const bool retired = !live && fin != kKeyMax;
+    int last = -1, sl = 0;  // the best candidate's last step and its slot there
+    int *hit;
+    if (live) {
       Cand cd;
       load_cand(P, (size_t)pos * G + best, cd);
-      write_result(P, pos, rec, cd.p, cd.c, cd.chi2, cd.nh, cd.nm, plen - 1, best, plen);
-    } else if (fin != kKeyMax) {
-      write_retired(P, pos, rec, fin, plen);
+      hit = write_state(P, pos, cd.p, cd.c, cd.chi2, cd.nh, cd.nm);
+      last = plen - 1;
+      sl = best;
+    } else if (retired) {
+      float p[6], c[21], chi2;
+      int fm;
+      GlobalRec{&P, pos}.get_fin(p, c, chi2, fm);
+      hit = write_state(P, pos, p, c, chi2, fm & 0xFF, (fm >> 8) & 0xFF);
+      last = fkey_step(fin) - 1;
+      sl = fkey_slot(fin);
     } else {
-      write_empty(P, pos, rec);
+      const float z[21] = {};
+      hit = write_state(P, pos, z, z, 0.f, 0, 0);
     }
+    for (int s0 = (plen - 1) & ~(kRows - 1); s0 >= 0 && plen > 0; s0 -= kRows) {
+      int v[kRows][G], h[kRows];
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) {
+        const int2 *row =
+            reinterpret_cast<const int2 *>(P.bp + ((size_t)min(s0 + i, plen - 1) * N + pos) * G);
+#pragma unroll
+        for (int j = 0; j < G / 2; ++j) {
+          const int2 w = row[j];
+          v[i][2 * j] = w.x;
+          v[i][2 * j + 1] = w.y;
+        }
+      }
+#pragma unroll
+      for (int i = kRows - 1; i >= 0; --i) {
+        const int s = s0 + i;
+        int w = v[i][0];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+          cnt += s + 1 < plen && v[i][j] >= 0;
+          if (j == sl) w = v[i][j];
+        }
+        h[i] = MKF_HIT_NONE;
+        if (s <= last) {
+          h[i] = (w >> 3) - 2;
+          sl = w & 7;
+        }
+      }
+      // (words past the plan's end are never read)
+      if (live || retired) {
+#pragma unroll
+        for (int i = 0; i < kRows; i += 4)
+          *reinterpret_cast<int4 *>(hit + s0 + i) = make_int4(h[i], h[i + 1], h[i + 2], h[i + 3]);
+      }
+    }
+    if (cnt) atomicAdd(&block_steps, (unsigned long long)cnt);
   }
   __syncthreads();
   if (threadIdx.x == 0 && block_steps) atomicAdd(P.n_steps, block_steps);
@@ -3135,7 +3188,8 @@ void launch_find_persistent(hipStream_t s, const FindParams &P, int grid_blocks,
 
 void launch_finalize(hipStream_t s, const FindParams &P) {
   if (P.n_seeds == 0) return;
-  hipLaunchKernelGGL(k_finalize, dim3(blocks_for(P.n_seeds, kTrackBlock)), dim3(kTrackBlock), 0, s, P);
+  const auto finalize = P.slots == 6 ? k_finalize<6> : k_finalize<8>;
+  hipLaunchKernelGGL(finalize, dim3(blocks_for(P.n_seeds, kTrackBlock)), dim3(kTrackBlock), 0, s, P);
 }
 void launch_check_results(hipStream_t s, const FindParams &P) {
   if (P.n_seeds == 0) return;

@@ -40,3 +40,33 @@ def test_tracks_do_not_depend_on_the_block_they_fall_in(flags):
         for got, want in zip(run(n), ref):
             assert got.tobytes() == np.ascontiguousarray(want[:n]).tobytes(), n
     c.close()
+
+
+@pytest.mark.parametrize("n_cand", [6, 8])
+def test_hit_histories_of_every_plan_length(n_cand):
+    """Plans that end on, before and behind a group of eight steps: the
+    layer-synchronous form, which follows the back-pointers from memory, gives
+    bitwise the persistent form's tracks and steps."""
+    import dataclasses
+    from paper_1811_04141_amd import mkf
+    from synth import Region
+    w = barrel_endcap(1, 300)
+    b = generate(w)
+    big = float(np.finfo(np.float32).max)
+    order = list(range(len(w.layers)))
+    got = {}
+    for flags in (0, mkf.F_BATCHED):
+        c = mkf.Context(dataclasses.replace(w.find, n_cand=n_cand), flags=flags)
+        c.load_geometry(w.layers)
+        for steps in (1, 7, 8, 9, 16, 17, 25):
+            c.load_steering((Region(-big, big, tuple(order[:steps + 3])),))
+            c.load_hits(b.ev_off, dev(b.x), dev(b.y), dev(b.z), dev(b.var_u), dev(b.var_v),
+                        dev(b.layer))
+            c.seed(dev(b.seed_event), dev(b.seed_hits))
+            c.find()
+            t = c.get_tracks(b.seed_hits.shape[0])
+            assert (t["plan_len"] == steps).any()
+            got.setdefault(steps, []).append((t.tobytes(), c.stats()["n_steps"]))
+        c.close()
+    for steps, (a, p) in got.items():
+        assert a == p, steps
