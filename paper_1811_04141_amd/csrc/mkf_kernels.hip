@@ -836,6 +836,7 @@ __global__ __launch_bounds__(256, kMat ? 1 : 4) void k_find_step(FindParams P, i
 // backward 100 to 82, results 29 to 26; 500,000 tracks: the backward fit's
 // head 148 to 140, its tail 235 to 234.
 constexpr int kTrackBlock = 64;
+constexpr int64_t kManyTracks = 1 << 18;  // tracks above which smoothing takes blocks of 256
 
 // Best of the final and the retired candidates of each seed (more hits,
 // then smaller chi2) and the count of candidate-layer steps (1 for the seed
@@ -2673,7 +2674,7 @@ constexpr int kSmFields = 91;
 constexpr int kSmFilt = 0, kSmPred = 27, kSmFC = 54, kSmLayer = 90;
 
 template <bool kExt>
-__global__ __launch_bounds__(kTrackBlock) void k_smooth_fwd(FindParams P, const int *seed_hits,
+__global__ __launch_bounds__(256) void k_smooth_fwd(FindParams P, const int *seed_hits,
                                                     float *wk, int *n_surf) {
   __shared__ DevLayer sl[kMaxLayers];
   stage_layers(P, sl);
@@ -2848,8 +2849,10 @@ __device__ __forceinline__ void chol_solve5(const float *Lp, const float *inv, f
 // tracks of 14 surfaces 100 us with general divisions and blocks of 256, 82 with
 // blocks of 64, 67 with the quotients of over() as well.  Eight lanes per track
 // with the matrices in LDS took 83, four 113: the factor is then taken by every
-// lane, and each surface waits for LDS four times.
-__global__ __launch_bounds__(kTrackBlock) void k_smooth_bwd(FindParams P, const float *wk,
+// lane, and each surface waits for LDS four times.  Two waves per SIMD: three
+// (153 registers) gain nothing on small calls, and on 2.5 M tracks of uneven
+// events their stores of single words to 64 rows meet in the L2 (4.08 against 4.01 ms).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_smooth_bwd(FindParams P, const float *wk,
                                                     const int *n_surf, float *out_par,
                                                     float *out_cov, int *out_n) {
   const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -3239,10 +3242,15 @@ void launch_smooth(hipStream_t s, const FindParams &P, const int *seed_hits, flo
                    int *n_surf, float *out_par, float *out_cov, int *out_n) {
   if (P.n_seeds == 0) return;
   const auto fwd = extended(P.cfg) ? k_smooth_fwd<true> : k_smooth_fwd<false>;
-  hipLaunchKernelGGL(fwd, dim3(blocks_for(P.n_seeds, kTrackBlock)), dim3(kTrackBlock), 0, s, P, seed_hits, wk,
-                     n_surf);
-  hipLaunchKernelGGL(k_smooth_bwd, dim3(blocks_for(P.n_seeds, kTrackBlock)), dim3(kTrackBlock), 0, s, P, wk,
-                     n_surf, out_par, out_cov, out_n);
+  // Where the chip is full many times over the two kernels are bound by HBM, and
+  // blocks of four wavefronts, which read and write a kilobyte of each field, are the
+  // faster: 2.5 M tracks of uneven events 6.23 ms against 6.50, of equal events
+  // 6.47 against 6.53.  At 131,000 tracks the two are equal (backward 273 and 270
+  // us), at 20,000 blocks of one take 67 against 82.
+  const int block = P.n_seeds <= kManyTracks ? kTrackBlock : 256;
+  const dim3 grid(blocks_for(P.n_seeds, block));
+  hipLaunchKernelGGL(fwd, grid, dim3(block), 0, s, P, seed_hits, wk, n_surf);
+  hipLaunchKernelGGL(k_smooth_bwd, grid, dim3(block), 0, s, P, wk, n_surf, out_par, out_cov, out_n);
 }
 
 // enough blocks to fill the device some times over, each a few hits long
