@@ -70,3 +70,33 @@ def test_hit_histories_of_every_plan_length(n_cand):
         c.close()
     for steps, (a, p) in got.items():
         assert a == p, steps
+
+
+def test_smoothing_of_more_tracks_than_one_wavefront_blocks_take():
+    """Above 262,144 tracks smoothing runs in blocks of four wavefronts: every
+    copy of a seed gets bitwise the states it gets in a call of 257 (a block and
+    one lane of either kind)."""
+    from paper_1811_04141_amd import mkf
+    w = barrel_endcap(1, 300)
+    b = generate(w)
+    c = mkf.Context(w.find, flags=mkf.F_BATCHED)
+    c.load_geometry(w.layers)
+    c.load_hits(b.ev_off, dev(b.x), dev(b.y), dev(b.z), dev(b.var_u), dev(b.var_v), dev(b.layer))
+    k, m = mkf.MAX_PLAN + 1, 257
+
+    def run(n):
+        at = np.arange(n) % m
+        c.seed(dev(b.seed_event[:m][at]), dev(b.seed_hits[:m][at]))
+        c.find()
+        out = [torch.zeros((n, k, 6), device="cuda"), torch.zeros((n, k, 21), device="cuda"),
+               torch.zeros(n, dtype=torch.int32, device="cuda")]
+        c.smooth(*out)
+        torch.cuda.synchronize()
+        return out
+
+    ref = run(m)
+    for n in (1 << 18, (1 << 18) + 1):
+        at = torch.arange(n, device="cuda") % m
+        for got, want in zip(run(n), ref):
+            assert torch.equal(got.view(torch.int32), want.view(torch.int32)[at]), n
+    c.close()
