@@ -59,6 +59,23 @@ constexpr int64_t kCopyRecords = 16384;
 constexpr int kCopyThreads = 8;
 constexpr int kCopyParts = 4;  // of a call that needs one slot (at most kCopyThreads)
 
+// The calling thread's device while a context's own is needed; the caller's
+// again afterwards.
+struct DeviceScope {
+  int before = -1;
+  hipError_t enter(int device) {
+    int d = -1;
+    hipError_t e = hipGetDevice(&d);
+    if (e != hipSuccess || d == device) return e;
+    e = hipSetDevice(device);
+    if (e == hipSuccess) before = d;
+    return e;
+  }
+  ~DeviceScope() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+};
+
 enum Stage { kCreated = 0, kGeometry = 1, kHits = 2, kSeeds = 3, kFound = 4 };
 
 }  // namespace
@@ -398,6 +415,8 @@ mkf_status mkf_create(const mkf_config *cfg, void *stream, mkf_ctx **out) {
   if (e == hipSuccess) e = hipEventCreate(&c->ev_b);
   if (e == hipSuccess) e = hipEventCreate(&c->ev_m0);
   if (e == hipSuccess) e = hipEventCreate(&c->ev_m1);
+  for (int k = 0; k < kCopyThreads && e == hipSuccess; ++k)
+    e = hipEventCreateWithFlags(&c->ev_copy[k], hipEventDisableTiming);
   if (e == hipSuccess)
     e = hipHostMalloc(reinterpret_cast<void **>(&c->h_cnt),
                       sizeof(unsigned long long) * kFindWords +
@@ -998,6 +1017,9 @@ mkf_status mkf_get_tracks(mkf_ctx *c, mkf_track *out, int64_t capacity, int64_t 
   };
   const int64_t n = std::min(capacity, c->n_seeds);
   if (n > 0) {
+    // (kernels and events want the context's device to be current)
+    DeviceScope scope;
+    HIP_TRY(c, scope.enter(c->device));
     const int slots = (int)std::min<int64_t>(kCopyThreads, (n + kCopyRecords - 1) / kCopyRecords);
     // (with several slots any of them may hold a whole chunk)
     const size_t records = (size_t)(slots == 1 ? n : slots * kCopyRecords);
@@ -1009,9 +1031,6 @@ mkf_status mkf_get_tracks(mkf_ctx *c, mkf_track *out, int64_t capacity, int64_t 
                                sizeof(mkf_track) * records, hipHostMallocDefault));
       c->h_tracks_n = records;
     }
-    for (int k = 0; k < kCopyThreads; ++k)
-      if (!c->ev_copy[k])
-        HIP_TRY(c, hipEventCreateWithFlags(&c->ev_copy[k], hipEventDisableTiming));
     const FindParams P = params(c);
     if (slots == 1) {
       // few records: in up to kCopyParts parts, so that the first are copied out

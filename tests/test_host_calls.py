@@ -1,0 +1,73 @@
+"""The library's host code against a runtime of two devices whose kernels do
+nothing (fake_hip.c): which device its calls are made on, what it allocates and
+what it launches.  CPU only; each test is a process of its own, so that the
+runtime is there before the library."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes as C, sys
+fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)
+fake.fake_launches.restype = fake.fake_wrong_what.restype = C.c_char_p
+import numpy as np
+from paper_1811_04141_amd import mkf
+from synth import generate, small_barrel
+w = small_barrel()
+b = generate(w)
+
+def context(n, flags=mkf.F_BATCHED, device=0):
+    '''A context of `device` with an event's seeds, repeated to n.'''
+    ctx = mkf.Context(w.find, flags=flags, stream=0x1000 + device)
+    ctx.load_geometry(w.layers)
+    ctx.load_hits(b.ev_off, b.x, b.y, b.z, b.var_u, b.var_v, b.layer)
+    seed(ctx, n)
+    return ctx
+
+def seed(ctx, n):
+    k = np.arange(n) % b.seed_hits.shape[0]
+    ctx.seed(np.ascontiguousarray(b.seed_event[k]), np.ascontiguousarray(b.seed_hits[k]))
+    ctx.find()
+
+def launches():
+    out = fake.fake_launches().decode().splitlines()
+    fake.fake_reset()
+    return out
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.run(["gcc", "-O1", "-std=c11", "-shared", "-fPIC", "-Wall", "-Werror", "-o", so,
+                    os.path.join(HERE, "fake_hip.c")], check=True)
+    return so
+
+
+def run(fake, body):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + body, fake], cwd=os.path.dirname(HERE),
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("n", [200, 40000])
+def test_tracks_are_fetched_on_the_contexts_device(fake, n):
+    """Records of one slot and of several, with another device current at the
+    call than at mkf_create: everything happens on the context's device, and
+    the caller's is current again afterwards."""
+    run(fake, f"""
+ctx = context({n})
+assert fake.fake_wrong() == 0, fake.fake_wrong_what()
+fake.fake_reset()
+fake.hipSetDevice(1)
+ctx.get_tracks({n})
+assert fake.fake_wrong() == 0, fake.fake_wrong_what()
+assert len(launches()) >= 1
+d = C.c_int(-1)
+fake.hipGetDevice(C.byref(d))
+assert d.value == 1
+""")
