@@ -301,7 +301,11 @@ mkf_status mkf_find(mkf_ctx *ctx);
  * (Section 2.2).  Writes the records of seeds 0 .. min(capacity, n_seeds) - 1
  * and nothing beyond; *n_total = n_seeds; returns MKF_E_CAPACITY if
  * capacity < n_seeds, MKF_E_ARG for capacity < 0, MKF_E_ORDER before a find.
- * Blocks until done. */
+ * The records pass through pinned host memory that the context keeps until it
+ * is destroyed: 0.3 MB for calls of up to 1,024 records, else 4.8 MB for each
+ * 16,384 records of the largest call so far, 38 MB at most.  A call of more than
+ * 16,384 records is helped by up to seven host threads that end before it
+ * returns.  Blocks until done. */
 mkf_status mkf_get_tracks(mkf_ctx *ctx, mkf_track *out, int64_t capacity, int64_t *n_total);
 
 /* Propagate n states to layers of the loaded geometry (unit access to the

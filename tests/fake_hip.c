@@ -74,7 +74,11 @@ int hipGetDevicePropertiesR0600(void *p, int d) { (void)p; (void)d; return kErro
 int hipDeviceSynchronize(void) { return kOk; }
 int hipMalloc(void **p, size_t n) { *p = calloc(1, n); return *p ? kOk : kError; }
 int hipFree(void *p) { free(p); return kOk; }
-int hipHostMalloc(void **p, size_t n, unsigned f) { (void)f; ++n_pinned; return hipMalloc(p, n); }
+int hipHostMalloc(void **p, size_t n, unsigned f) {
+  (void)f;
+  __atomic_add_fetch(&n_pinned, 1, __ATOMIC_RELAXED);
+  return hipMalloc(p, n);
+}
 int hipHostFree(void *p) { free(p); return kOk; }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) {
   (void)k; (void)st;

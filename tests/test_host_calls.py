@@ -71,3 +71,24 @@ d = C.c_int(-1)
 fake.hipGetDevice(C.byref(d))
 assert d.value == 1
 """)
+
+
+def test_growing_calls_pin_each_slot_once(fake):
+    """Events of slowly growing size: a small first slot, then the whole of it,
+    then the other seven as calls need them; nothing is pinned again."""
+    run(fake, """
+ctx = context(200)
+fake.fake_reset()
+for n in range(100, 1025, 77):
+    seed(ctx, n)
+    ctx.get_tracks(n)
+assert fake.fake_pinned() == 1, fake.fake_pinned()
+for n in list(range(1100, 16385, 407)) + [16384]:
+    seed(ctx, n)
+    ctx.get_tracks(n)
+assert fake.fake_pinned() == 2, fake.fake_pinned()
+for n in (16385, 30000, 60000, 200000, 150000, 50):
+    seed(ctx, n)
+    ctx.get_tracks(n)
+assert fake.fake_pinned() <= 2 + 7, fake.fake_pinned()
+""")
