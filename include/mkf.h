@@ -426,8 +426,9 @@ mkf_status mkf_get_stats(mkf_ctx *ctx, mkf_stats *out);
 
 /* Launch shape of the persistent find (MKF_F_BATCHED) and binning of the
  * hit index.  Results do not depend on it (tested bit for bit).  Until one is
- * set or found by the autotuner, the launch shape follows the number of seeds
- * (mkf_get_tuning then reports the starting values). */
+ * set or found by the autotuner, the launch shape follows the number of seeds;
+ * mkf_get_tuning then reports the starting values, and setting these back (with
+ * other bins or another lane group, say) leaves it so. */
 typedef struct {
   int32_t waves_per_simd; /* register budget of the persistent kernel, 1..4
                              (more waves hide more latency, but spill) */

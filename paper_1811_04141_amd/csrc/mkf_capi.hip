@@ -183,7 +183,7 @@ struct mkf_ctx {
   int device = 0;  // the device current at mkf_create
   std::string arch;
   mkf_tuning tuning{2, 8, 0, 0, 0};
-  bool tuned = false;  // a tuning was set: its launch shape is used as it is
+  bool tuned = false;  // a launch shape was set: it is used as it is
 
   // learned surrogate: master weights, Adam moments, BF16 images, counters
   DevBuf d_mlp_param, d_mlp_m, d_mlp_v, d_W1p, d_W2p, d_W3p, d_W2T, d_W3T, d_mb1, d_mb2, d_mb3;
@@ -907,7 +907,7 @@ static void launch_shape(const mkf_ctx *c, int &waves, int &blocks_per_cu) {
   waves = c->tuning.waves_per_simd;
   blocks_per_cu = c->tuning.blocks_per_cu;
   if (c->tuned) return;
-  const int seeds = c->cfg.n_cand > 6 ? 8 : 10;
+  const int seeds = c->cfg.n_cand > 6 || c->tuning.lane_group == 8 ? 8 : 10;
   const int64_t tiles = (c->n_seeds + seeds - 1) / seeds, simds = 4 * (int64_t)c->n_cu;
   const bool all_in_four = tiles > 3 * simds && tiles <= 4 * simds;
   waves = tiles <= 2 * simds ? 2
@@ -1329,7 +1329,6 @@ mkf_status apply_tuning(mkf_ctx *c, const mkf_tuning &t) {
   const bool rebin =
       t.phi_bin_shift != c->tuning.phi_bin_shift || t.q_bin_shift != c->tuning.q_bin_shift;
   c->tuning = t;
-  c->tuned = true;
   drop_graph(c);
   if (!rebin || c->n_layers == 0) return MKF_OK;
   mkf_status st = upload_layers(c);
@@ -1344,6 +1343,9 @@ extern "C" {
 mkf_status mkf_set_tuning(mkf_ctx *c, const mkf_tuning *t) {
   if (!c) return MKF_E_ARG;
   if (!t || !tuning_ok(c, *t)) return fail(c, MKF_E_ARG, "tuning out of range");
+  // the starting values set back, say with other bins, set no shape
+  if (t->waves_per_simd != c->tuning.waves_per_simd || t->blocks_per_cu != c->tuning.blocks_per_cu)
+    c->tuned = true;
   return apply_tuning(c, *t);
 }
 
@@ -1387,6 +1389,7 @@ mkf_status mkf_autotune(mkf_ctx *c, int32_t repeats, const char *cache_path, mkf
       }
       fclose(f);
       if (found) {
+        c->tuned = true;
         mkf_status st = apply_tuning(c, hit);
         if (st == MKF_OK && best) *best = hit;
         return st;
@@ -1397,6 +1400,7 @@ mkf_status mkf_autotune(mkf_ctx *c, int32_t repeats, const char *cache_path, mkf
   c->cfg.flags &= ~MKF_F_GRAPH;  // time eager launches
   const mkf_tuning keep = c->tuning;
   const bool keep_tuned = c->tuned;
+  c->tuned = true;
   mkf_tuning win = c->tuning;
   float win_ms = 1e30f;
   mkf_status st = MKF_OK;

@@ -92,3 +92,35 @@ for n in (16385, 30000, 60000, 200000, 150000, 50):
     ctx.get_tracks(n)
 assert fake.fake_pinned() <= 2 + 7, fake.fake_pinned()
 """)
+
+
+@pytest.mark.parametrize("n", [200, 25000, 40000, 100000])
+def test_a_tuning_read_and_set_back_keeps_the_launch(fake, n):
+    """mkf_get_tuning's values set back, as they are or with other bins, leave the
+    find's launch as it was: by the number of seeds where no shape was set, and
+    the shape that was set where one was."""
+    run(fake, f"""
+def find_launch():
+    fake.fake_reset()
+    ctx.find()
+    return [l for l in launches() if "k_find_persistent" in l]
+
+ctx = context({n})
+own = find_launch()
+assert len(own) == 1
+t = ctx.get_tuning()
+ctx.set_tuning(**t)
+assert find_launch() == own and ctx.get_tuning() == t
+ctx.set_tuning(**dict(t, phi_bin_shift=1))
+assert find_launch() == own
+ctx.set_tuning(1, 1)
+one = find_launch()
+assert one != own
+ctx.set_tuning(**dict(ctx.get_tuning(), q_bin_shift=-1))
+assert find_launch() == one
+ctx.set_tuning(2, 8)  # set after another: as it is
+two = find_launch()
+seed(ctx, 200000)
+big = find_launch()
+assert "ILi2E" in two[0] and "ILi2E" in big[0] and big[0].split()[1] == "2048"
+""")
