@@ -361,21 +361,33 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
 
 // A window of more than kWideBins bins or kWideRows rows (a candidate whose
 // state is poorly measured: its window may span the whole layer) is scanned by
-// the wavefront's lanes together; alone its lane would hold up the other 63 for
+// the lanes that are here together; alone its lane would hold up the others for
 // hundreds of hits.  Below the line a lane is done in one or two passes of four
 // hits, about what the hand-over costs; lines at 24 bins and 3 rows and at 128
 // and 8 measured within 1.5% of this one.
-constexpr int kWideBins = 48, kWideRows = 5;
+//
+// Lanes that scan by themselves do so at the same time, windows scanned together
+// come one after the other, and only the lanes with a live candidate that crosses
+// the layer are here: one of 6 or 8 at a seed's first step, fewer in a small
+// call.  So at most one lane in kWideShare hands its window over; where more are
+// above the line, it rises by factors of four until only the widest are.  At 30 and
+// 10 times the usual scattering and cuts of 30 and 200, layer form: 64 seeds 749 to
+// 439 us (no hand-over 422), 5,000 seeds 2.30 to 1.26 ms (3.48), 64 and 5,000 seeds
+// of the persistent form 522 to 285 and 986 to 446 us, against handing over all of
+// them.  Shares of 4 and 16: 465 and 399 us, 1.40 and 2.09 ms, 284 and 232 us, 437
+// and 677 us; the usual windows are the same up to 12 and 5% slower at 16.
+constexpr int kWideBins = 48, kWideRows = 5, kWideShare = 8;
 
 // The scan of lane o's window by every lane that is here: the lanes look up
 // one run of bins each, then score the runs' hits one per lane; compatible hits
 // go to lane o's list.  Lane o's values are read into scalar registers, so
 // that this costs the kernels no more than two vector registers.  Bound, like
 // the lane's own scan, by the latency of the run bounds and of the hits, here
-// paid once per 64 of them.  Find kernel without and with it: 2 events x 5,000
-// seeds 0.250 and 0.104 ms, 4 events x 28,000 triplet seeds 0.565 and 0.456 ms,
-// 100 events x 5,000 seeds 1.56 and 1.40 ms (3 waves per SIMD); without it
-// single tiles of 10 seeds took up to 500 us and the launch ended on them.
+// paid once per as many of them as lanes are here.  Find kernel without and with
+// it: 2 events x 5,000 seeds 0.250 and 0.104 ms, 4 events x 28,000 triplet seeds
+// 0.565 and 0.456 ms, 100 events x 5,000 seeds 1.56 and 1.40 ms (3 waves per SIMD);
+// without it single tiles of 10 seeds took up to 500 us and the launch ended on
+// them.
 template <int N>
 __device__ __forceinline__ void scan_wide(const FindParams &P, const DevLayer &L, int o,
                                           const Prop &pr, const Frame &f, float chi2_base, int nh,
@@ -454,9 +466,15 @@ __device__ __forceinline__ void scan_window(const FindParams &P, const DevLayer 
   window_bins(P, L, ev, pr, f, base, qlo, qhi, seg);
   const int rows = qhi - qlo + 1;
   const int width = seg[1] - seg[0] + 1 + max(seg[3] - seg[2] + 1, 0);
-  const bool wide = rows > kWideRows || rows * width > kWideBins;
+  const int bins = rows * width;
+  bool wide = rows > kWideRows || bins > kWideBins;
   unsigned long long wides = __ballot(wide);
-  if (wides != 0ull) {
+  if (__builtin_expect(wides != 0ull, 0)) {
+    const int n_here = __popcll(__ballot(true));
+    for (int line = 4 * kWideBins; kWideShare * __popcll(wides) > n_here; line *= 4) {
+      wide = bins > line;
+      wides = __ballot(wide);
+    }
     for (; wides != 0ull; wides &= wides - 1)
       scan_wide(P, L, __ffsll(wides) - 1, pr, f, chi2_base, nh, slot, base, qlo, qhi, seg, lst,
                 n_ext, n_near);
