@@ -157,6 +157,7 @@ struct mkf_ctx {
   // triplet seeding: counts (with cursors), offsets, scan scratch, kept triplets
   DevBuf d_tr_cnt, d_tr_off, d_tr_tmp, d_tr_kept, d_tr_at;
   DevBuf d_dup_h, d_dup_n, d_dup_cnt, d_dup_off, d_dup_fill, d_dup_list, d_dup_tmp, d_dup_total;
+  DevBuf d_clean_key;  // seed cleaning: what a pair of seeds is compared by
   std::vector<int64_t> active_at_step;  // seeds (in processing order) with plan_len > step
   int max_plan_len = 0;
   int64_t n_seeds_ok = 0;
@@ -200,7 +201,7 @@ struct mkf_ctx {
                      &d_bp, &d_out, &d_mlp_param, &d_mlp_m, &d_mlp_v, &d_W1p,
                      &d_W2p, &d_W3p, &d_W2T, &d_W3T, &d_mb1, &d_mb2, &d_mb3, &d_cnt, &d_radii,
                      &d_tx, &d_tt, &d_tvalid, &d_partial, &d_partial2, &d_loss, &d_grad, &d_bf_tmp, &d_sm_wk, &d_sm_n, &d_tr_cnt, &d_tr_off, &d_tr_tmp, &d_tr_kept, &d_tr_at, &d_dup_h, &d_dup_n, &d_dup_cnt, &d_dup_off,
-                     &d_dup_fill, &d_dup_list, &d_dup_tmp, &d_dup_total, &d_seed_chi2, &d_seed_fit};
+                     &d_dup_fill, &d_dup_list, &d_dup_tmp, &d_dup_total, &d_clean_key, &d_seed_chi2, &d_seed_fit};
     for (DevBuf *b : all) b->release();
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -1276,6 +1277,7 @@ mkf_status mkf_clean_seeds(mkf_ctx *c, const mkf_cleaning *cc, int32_t *out_keep
   const size_t N = (size_t)c->n_seeds, H = (size_t)std::max<int64_t>(c->n_hits, 1);
   // the duplicate-removal scratch serves here too (3 hits per seed)
   HIP_TRY(c, c->d_dup_h.ensure(sizeof(int) * 3 * N));
+  HIP_TRY(c, c->d_clean_key.ensure(sizeof(float) * 3 * N));
   HIP_TRY(c, c->d_dup_cnt.ensure(sizeof(int) * H));
   HIP_TRY(c, c->d_dup_off.ensure(sizeof(int) * (H + 1)));
   HIP_TRY(c, c->d_dup_fill.ensure(sizeof(int) * H));
@@ -1288,14 +1290,14 @@ mkf_status mkf_clean_seeds(mkf_ctx *c, const mkf_cleaning *cc, int32_t *out_keep
   launch_fill_i32(c->stream, c->d_dup_fill.as<int>(), (int64_t)H, 0);
   launch_fill_i32(c->stream, c->d_dup_total.as<int>(), 1, 0);
   launch_clean_prep(c->stream, P, c->d_seed_hits.as<int>(), c->d_dup_h.as<int>(),
-                    c->d_dup_cnt.as<int>());
+                    c->d_clean_key.as<float>(), c->d_dup_cnt.as<int>());
   launch_scan(c->stream, c->d_dup_cnt.as<int>(), c->d_dup_off.as<int>(), (int64_t)H,
               c->d_dup_tmp.as<int>());
   launch_clean_fill(c->stream, P, c->d_dup_h.as<int>(), c->d_dup_off.as<int>(),
                     c->d_dup_fill.as<int>(), c->d_dup_list.as<int>());
   launch_clean_decide(c->stream, P, c->d_seed_hits.as<int>(), c->d_seed_chi2.as<float>(),
-                      c->d_dup_h.as<int>(), c->d_dup_off.as<int>(), c->d_dup_list.as<int>(), dc,
-                      out_keep, c->d_dup_total.as<int>());
+                      c->d_dup_h.as<int>(), c->d_clean_key.as<float>(), c->d_dup_off.as<int>(),
+                      c->d_dup_list.as<int>(), dc, out_keep, c->d_dup_total.as<int>());
   HIP_TRY(c, hipGetLastError());
   int total = 0;
   HIP_TRY(c, hipMemcpyAsync(&total, c->d_dup_total.ptr, sizeof(int), hipMemcpyDeviceToHost,

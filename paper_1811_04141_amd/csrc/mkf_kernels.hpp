@@ -160,13 +160,15 @@ void launch_dup_decide(hipStream_t s, const FindParams &P, const int *seed_hits,
 struct DevCleaning {
   float tol_ipt, tol_eta, tol_phi;
 };
+// (key: 3 n_seeds words)
 void launch_clean_prep(hipStream_t s, const FindParams &P, const int *seed_hits, int *hbuf,
-                       int *cnt);
+                       float *key, int *cnt);
 void launch_clean_fill(hipStream_t s, const FindParams &P, const int *hbuf, const int *off,
                        int *fill, int *list);
 void launch_clean_decide(hipStream_t s, const FindParams &P, const int *seed_hits,
-                         const float *seed_chi2, const int *hbuf, const int *off,
-                         const int *list, const DevCleaning &cc, int *out_keep, int *n_keep);
+                         const float *seed_chi2, const int *hbuf, const float *key,
+                         const int *off, const int *list, const DevCleaning &cc, int *out_keep,
+                         int *n_keep);
 // The hits as the caller gave them (x == nullptr: the records already in byorig)
 // into records, checked (a bad one sets *bad, host memory the device can write),
 // and their bins counted: bin_rank[i] is hit i's bin and its rank there (a bad
