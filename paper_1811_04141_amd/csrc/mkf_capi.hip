@@ -1206,7 +1206,7 @@ mkf_status mkf_make_seeds(mkf_ctx *c, const mkf_seeding *sc, int64_t capacity,
   int64_t max_ev = 0;
   for (int e = 0; e < c->n_events; ++e) max_ev = std::max(max_ev, c->ev_off[e + 1] - c->ev_off[e]);
   launch_fill_i32(c->stream, cnt, n + n_cursor, 0);
-  launch_triplets(c->stream, P, ds, max_ev, cnt, st);
+  launch_triplets(c->stream, P, ds, n, max_ev, cnt, st);
   HIP_TRY(c, hipGetLastError());
   launch_scan(c->stream, cnt, c->d_tr_off.as<int>(), n, c->d_tr_tmp.as<int>());
   HIP_TRY(c, hipGetLastError());
@@ -1220,7 +1220,7 @@ mkf_status mkf_make_seeds(mkf_ctx *c, const mkf_seeding *sc, int64_t capacity,
   *n_total = total;
   if (total > capacity)
     return fail(c, MKF_E_CAPACITY, "%d triplets, capacity %lld", total, (long long)capacity);
-  launch_triplets_write(c->stream, P, ds, max_ev, cnt, c->d_tr_off.as<int>(), st,
+  launch_triplets_write(c->stream, P, ds, n, max_ev, cnt, c->d_tr_off.as<int>(), st,
                         c->h_len[1] > 0, out_event, out_hits);
   HIP_TRY(c, hipGetLastError());
   HIP_TRY(c, hipStreamSynchronize(c->stream));

@@ -139,12 +139,13 @@ struct TripletStore {
   int2 *kept;
 };
 // counts[i]: triplets whose first hit is the hit at binned position i (the
-// other positions are left alone).  max_event_hits bounds the hits of one event.
-void launch_triplets(hipStream_t s, const FindParams &P, const DevSeeding &sc,
+// other positions are left alone).  n_hits: of all events; max_event_hits bounds the hits
+// of one event.
+void launch_triplets(hipStream_t s, const FindParams &P, const DevSeeding &sc, int64_t n_hits,
                      int64_t max_event_hits, int *counts, const TripletStore &st);
 // the triplets (event, three event-local hit indices) to their places
 void launch_triplets_write(hipStream_t s, const FindParams &P, const DevSeeding &sc,
-                           int64_t max_event_hits, int *counts, const int *offsets,
+                           int64_t n_hits, int64_t max_event_hits, int *counts, const int *offsets,
                            const TripletStore &st, bool again, int *out_event, int *out_hits);
 // duplicate-track removal: per track its sorted hits (hbuf [n_seeds][kDupStride],
 // hn), the tracks on every hit (CSR: cnt, off, fill, list), the decision

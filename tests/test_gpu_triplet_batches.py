@@ -1,0 +1,89 @@
+"""Triplet seeding of batches whose events differ in size."""
+import time
+
+import numpy as np
+import pytest
+
+from synth import SeedingConfig, barrel_endcap, generate_event
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+FIELDS = ("x", "y", "z", "var_u", "var_v", "layer")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def batch(events):
+    off = np.concatenate([[0], np.cumsum([len(e.x) for e in events])])
+    return off, [dev(np.concatenate([getattr(e, f) for e in events])) for f in FIELDS]
+
+
+class Seeder:
+    def __init__(self, w, cap=1 << 20):
+        from paper_1811_04141_amd import mkf
+        self.ctx = mkf.Context(w.find)
+        self.ctx.load_geometry(w.layers)
+        self.ev = torch.empty(cap, dtype=torch.int32, device="cuda")
+        self.hits = torch.empty((cap, 3), dtype=torch.int32, device="cuda")
+        self.cap = cap
+
+    def load(self, events):
+        off, arrs = batch(events)
+        self.ctx.load_hits(off, *arrs)
+
+    def seeds(self):
+        n = self.ctx.make_seeds(SeedingConfig(), self.cap, self.ev, self.hits)
+        t = torch.cat([self.ev[:n, None], self.hits[:n]], 1).cpu().numpy()
+        return t[np.lexsort(t.T[::-1])]
+
+    def ms(self):
+        best = 1e30
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            self.ctx.make_seeds(SeedingConfig(), self.cap, self.ev, self.hits)
+            best = min(best, time.perf_counter() - t)
+        return best * 1e3
+
+
+@pytest.mark.parametrize("sizes", [(1500, 2000), (300, 3), (0, 1), (0, 7)])
+def test_large_event_among_small_ones(sizes):
+    """One event of many tracks and many of five, the large one first, last and
+    between: each event's triplets are those it has alone."""
+    tracks, n_small = sizes
+    w = barrel_endcap()
+    big = [generate_event(w, 0, n_tracks=tracks)] if tracks else []
+    small = generate_event(w, 1, n_tracks=5)
+    s = Seeder(w)
+    alone = []
+    for e in big + [small]:
+        s.load([e])
+        alone.append(s.seeds()[:, 1:])
+    for at in sorted({0, n_small // 2, n_small}):
+        events = [small] * n_small
+        events[at:at] = big
+        s.load(events)
+        got = s.seeds()
+        want = [np.column_stack([np.full(len(a), e), a])
+                for e in range(len(events)) for a in [alone[0 if events[e] is not small else -1]]]
+        assert np.array_equal(got, np.concatenate(want))
+    s.ctx.close()
+
+
+def test_large_event_costs_little_more_among_small_ones():
+    """An event of 3,000 tracks among 2,000 of five takes at most four times as long
+    as alone and the others without it (9.6 times when every event got the same
+    share of the wavefronts whatever its size, 1.3 now)."""
+    w = barrel_endcap()
+    big, small = generate_event(w, 0, n_tracks=3000), generate_event(w, 1, n_tracks=5)
+    s = Seeder(w)
+    ms = []
+    for events in ([big], [small] * 2000, [big] + [small] * 2000):
+        s.load(events)
+        ms.append(s.ms())
+    s.ctx.close()
+    assert ms[2] < 4.0 * (ms[0] + ms[1]), ms
