@@ -3287,7 +3287,10 @@ void launch_smooth(hipStream_t s, const FindParams &P, const int *seed_hits, flo
 // event gets as many, and blocks that find nothing cost 1.2 ns each where a
 // first-layer hit, one in eleven, takes its wavefront some 20 us: the sum of both
 // is least near the square root below.  An event of 3,000 tracks among 15,000 of 5
-// takes 1.2 ms, 23 with one block per event; among 200, 0.20 ms (0.40).
+// takes 1.2 ms, 23 with one block per event; among 200, 0.20 ms (0.40).  The number
+// is odd: blocks go round the XCDs and the segments of the store in turn, and
+// in small events only the first few have a hit, so that with eight per event two
+// XCDs did the work (2,000 events of 5 tracks 208 us, 112 with nine).
 constexpr int kTripletBlocks = 16384;
 static dim3 triplet_grid(const FindParams &P, int64_t n_hits, int64_t max_event_hits,
                          int per_block) {
@@ -3296,8 +3299,8 @@ static dim3 triplet_grid(const FindParams &P, int64_t n_hits, int64_t max_event_
   const double most = std::max((double)kTripletBlocks, std::sqrt(400.0 * max * P.n_events)) /
                       P.n_events;
   const int64_t per_event = std::max<int64_t>(1, (int64_t)std::min(share, most));
-  return dim3((unsigned)std::min<int64_t>((max_event_hits + per_block - 1) / per_block, per_event),
-              (unsigned)P.n_events);
+  const int64_t x = std::min<int64_t>((max_event_hits + per_block - 1) / per_block, per_event);
+  return dim3((unsigned)x | 1u, (unsigned)P.n_events);
 }
 
 void launch_triplets(hipStream_t s, const FindParams &P, const DevSeeding &sc, int64_t n_hits,

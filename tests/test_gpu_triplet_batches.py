@@ -87,3 +87,18 @@ def test_large_event_costs_little_more_among_small_ones():
         ms.append(s.ms())
     s.ctx.close()
     assert ms[2] < 4.0 * (ms[0] + ms[1]), ms
+
+
+def test_small_events_use_the_whole_device():
+    """2,000 events of five tracks take about as long as 1,800.  (Twice as long when
+    2,000 got eight blocks per event, of which the first two have hits and always
+    ran on the same two XCDs, and 1,800 nine.)"""
+    w = barrel_endcap()
+    small = generate_event(w, 1, n_tracks=5)
+    s = Seeder(w)
+    ms = []
+    for n in (1800, 2000):
+        s.load([small] * n)
+        ms.append(s.ms())
+    s.ctx.close()
+    assert ms[1] < 1.5 * ms[0], ms
