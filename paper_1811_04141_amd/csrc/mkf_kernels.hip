@@ -1752,17 +1752,24 @@ __device__ __forceinline__ int wave_inclusive(int v, int lane) {
 //     waves per SIMD: 2.80 ms on 20 events x 5,000 tracks, where gathering takes
 //     2.05 at six waves per SIMD (2.30 at four) and the cuts 0.04.)
 //   count, write: the same with the cuts, for the hits that did not fit.
+// A lane notes a few c per walk, and the walk is repeated where one has more: the
+// usual cuts leave few.  Loose ones leave hundreds, so gathering hands a hit over
+// after kTripletRounds walks or as soon as its list is known to be too short, and
+// the other modes note 32 at a time.  (With four in all modes, and gathered triplets
+// counted before they were put: 66 million triplets of 20 events x 500 tracks 1.10 s,
+// now 0.13; d0_max 1 cm on an event of 5,000 tracks 42 ms, now 5.9.)
 enum TripletMode { kGather = 0, kCount = 1, kWriteOut = 2 };
-constexpr int kTripletKeep = 4;  // c that a lane notes per walk
+constexpr int kTripletRounds = 4;
 constexpr int kTripletList = 256;
 template <int kMode>
-__global__ __launch_bounds__(256, kMode == kGather ? 6 : 1) void k_triplets(FindParams P, DevSeeding sc, int *counts,
-                                                  const int *offsets, TripletStore st,
-                                                  int *out_event, int *out_hits) {
+__global__ __launch_bounds__(256, kMode == kGather ? 6 : 1) void k_triplets(
+    FindParams P, DevSeeding sc, int *counts, const int *offsets, TripletStore st, int *out_event,
+    int *out_hits) {
+  constexpr int kKeep = kMode == kGather ? 4 : 32;  // c that a lane notes per walk
   __shared__ DevLayer sl[kMaxLayers];
   __shared__ int s_shift[4][64], s_end[4][64];  // runs of b: sorted position - ordinal, end ordinal
   __shared__ int s_pair[4][128];                // sorted positions of the gathered b
-  __shared__ int s_c[4][kTripletKeep][64];
+  __shared__ int s_c[4][kKeep][64];
   __shared__ int2 s_list[4][kMode == kGather ? kTripletList : 1];  // the hit's (b, c) so far
   if (kMode != kGather && *st.n_again == 0) return;
   stage_layers(P, sl);
@@ -1785,6 +1792,7 @@ __global__ __launch_bounds__(256, kMode == kGather ? 6 : 1) void k_triplets(Find
     int total = 0, n_pair = 0;  // (the same in all lanes)
     // up to 64 gathered pairs, one per lane
     auto take_pairs = [&](int n) {
+      if (kMode == kGather && total > kTripletList) return;  // handed over
       const bool on = lane < n;
       const int kb = s_pair[wv][on ? lane : 0];
       const HitRec hb = P.sorted[kb];
@@ -1798,10 +1806,10 @@ __global__ __launch_bounds__(256, kMode == kGather ? 6 : 1) void k_triplets(Find
       const int qhi = clampi((int)floorf((zp + hw - L2.q_lo) * L2.q_scale), 0, L2.nq - 1);
       const PhiRuns runs = phi_runs(L2, atan2f(hb.y, hb.x), dphi2);
       const int base = ev0 + L2.bin_base;
-      // Rounds of kTripletKeep noted c per lane, the walk repeated where a lane
-      // has more; when all are counted, the places are known and the triplets
-      // are put there, from the notes if there was one round, else in the same
-      // rounds again.
+      // Rounds of kKeep noted c per lane, the walk repeated where a lane has more;
+      // when all are counted, the places are known and the triplets are put
+      // there, from the notes if there was one round, else in the same rounds
+      // again.  (Gathering counts all that are noted: known after one walk.)
       int noted = 0, most = 0, n_c = 0, incl = 0, skip = 0;
       int64_t pos = 0;
       bool putting = false;
@@ -1809,27 +1817,38 @@ __global__ __launch_bounds__(256, kMode == kGather ? 6 : 1) void k_triplets(Find
         int ord = 0;
         walk_runs(P, base, L2.nphi, runs, qlo, on ? qhi : qlo - 1, [&](int c, const float4 &h) {
           if (triplet_may_pass(sc, ax, ay, az, ra, ux, uy, u2, hb.x, hb.y, Z, h.x, h.y, h.z)) {
-            if (ord >= skip && ord < skip + kTripletKeep) s_c[wv][ord - skip][lane] = c;
+            if (ord >= skip && ord < skip + kKeep) s_c[wv][ord - skip][lane] = c;
             ++ord;
           }
         });
         if (!putting && skip == 0) {
           noted = ord;
-          while (__ballot(noted > most) != 0ull) most += kTripletKeep;
-        }
-        int pass = 0;  // which of this round's c pass
-#pragma unroll 1
-        for (int t = 0; t < kTripletKeep; ++t) {
-          if (skip + t >= noted) break;
+          while (__ballot(noted > most) != 0ull) most += kKeep;
+          if (most == 0) return;
           if constexpr (kMode == kGather) {
-            pass |= 1 << t;
-            continue;
+            incl = wave_inclusive(noted, lane);
+            const int all = total + __shfl(incl, 63);
+            if (most > kTripletRounds * kKeep || all > kTripletList) {
+              total = kTripletList + 1;
+              return;
+            }
+            pos = total + incl - noted;
+            putting = true;
           }
-          const HitRec hc = P.sorted[s_c[wv][t][lane]];
-          if (triplet_passes(P.cfg, sc, ax, ay, az, hb.x, hb.y, hb.z, hc.x, hc.y, hc.z))
-            pass |= 1 << t;
         }
-        skip += kTripletKeep;
+        unsigned pass = 0;  // which of this round's c pass
+        if constexpr (kMode == kGather) {
+          pass = (1u << clampi(noted - skip, 0, kKeep)) - 1u;
+        } else {
+#pragma unroll 1
+          for (int t = 0; t < kKeep; ++t) {
+            if (skip + t >= noted) break;
+            const HitRec hc = P.sorted[s_c[wv][t][lane]];
+            if (triplet_passes(P.cfg, sc, ax, ay, az, hb.x, hb.y, hb.z, hc.x, hc.y, hc.z))
+              pass |= 1u << t;
+          }
+        }
+        skip += kKeep;
         if (!putting) {
           n_c += __popc(pass);
           if (skip < most) continue;
@@ -1837,11 +1856,13 @@ __global__ __launch_bounds__(256, kMode == kGather ? 6 : 1) void k_triplets(Find
           pos = (kMode == kWriteOut ? (int64_t)offsets[idx] : 0) + total + incl - n_c;
           if (kMode == kCount) break;
           putting = true;
-          skip = 0;
-          if (most > kTripletKeep) continue;
+          if (most > kKeep) {
+            skip = 0;
+            continue;
+          }
         }
 #pragma unroll 1
-        for (int t = 0; t < kTripletKeep; ++t)
+        for (int t = 0; t < kKeep; ++t)
           if ((pass >> t) & 1) {
             const int kc = s_c[wv][t][lane];
             if constexpr (kMode == kWriteOut) {
@@ -1849,12 +1870,12 @@ __global__ __launch_bounds__(256, kMode == kGather ? 6 : 1) void k_triplets(Find
               out_hits[3 * pos] = ha.orig;
               out_hits[3 * pos + 1] = hb.orig;
               out_hits[3 * pos + 2] = P.sorted[kc].orig;
-            } else if (pos < kTripletList) {
+            } else {
               s_list[wv][pos] = make_int2(kb, kc);
             }
             ++pos;
           }
-        if (skip >= most || most <= kTripletKeep) break;
+        if (skip >= most) break;
       }
       total += __shfl(incl, 63);
     };

@@ -40,12 +40,12 @@ class Seeder:
         t = torch.cat([self.ev[:n, None], self.hits[:n]], 1).cpu().numpy()
         return t[np.lexsort(t.T[::-1])]
 
-    def ms(self):
+    def ms(self, cuts=SeedingConfig()):
         best = 1e30
         for _ in range(8):
             torch.cuda.synchronize()
             t = time.perf_counter()
-            self.ctx.make_seeds(SeedingConfig(), self.cap, self.ev, self.hits)
+            self.ctx.make_seeds(cuts, self.cap, self.ev, self.hits)
             best = min(best, time.perf_counter() - t)
         return best * 1e3
 
@@ -102,3 +102,41 @@ def test_small_events_use_the_whole_device():
         ms.append(s.ms())
     s.ctx.close()
     assert ms[1] < 1.5 * ms[0], ms
+
+
+LOOSE = SeedingConfig(d0_max=1.0)
+
+
+def test_loose_cuts_on_dense_events():
+    """Hundreds of candidates per pair, most of which fail: the set is the one that
+    the exact cuts leave of any larger bound, here of d0_max 1.05."""
+    from oracle import oracle as O
+    w = barrel_endcap()
+    e = generate_event(w, 0, n_tracks=1200, phi_range=(0.0, 1.0))
+    s = Seeder(w)
+    s.load([e])
+    got = {}
+    for d0 in (1.0, 1.05):
+        n = s.ctx.make_seeds(SeedingConfig(d0_max=d0), s.cap, s.ev, s.hits)
+        got[d0] = {tuple(h) for h in s.hits[:n].cpu().numpy().tolist()}
+        assert len(got[d0]) == n
+    s.ctx.close()
+    assert got[1.0] < got[1.05]
+    for t in sorted(got[1.05] - got[1.0]):
+        xyz = [[e.x[i], e.y[i], e.z[i]] for i in t]
+        assert O.triplet_params(w.find, LOOSE, *xyz)[1] < 1e-9
+    for t in sorted(got[1.0])[::37]:
+        xyz = [[e.x[i], e.y[i], e.z[i]] for i in t]
+        assert O.triplet_params(w.find, LOOSE, *xyz)[1] > -1e-9
+
+
+def test_loose_cuts_cost_by_the_candidates():
+    """d0_max 1 cm against 0.1 widens the windows and leaves far more candidates to
+    the exact cuts.  (89 times as long when walks were repeated for every four
+    candidates of a pair, 14 now.)"""
+    w = barrel_endcap()
+    s = Seeder(w)
+    s.load([generate_event(w, 0, n_tracks=3000)])
+    ms = [s.ms(), s.ms(LOOSE)]
+    s.ctx.close()
+    assert ms[1] < 35.0 * ms[0], ms
