@@ -21,6 +21,7 @@
 #include <cmath>
 
 #include "mkf_kernels.hpp"
+#include "mkf_quotient.hpp"
 
 namespace mkf {
 
@@ -2855,19 +2856,6 @@ __device__ __forceinline__ void sandwich5(const FreeCoords &J, const float *M, f
 #pragma unroll
     for (int a = b; a < 5; ++a) out[a * (a + 1) / 2 + b] = u[a];
   }
-}
-
-// a / d, inv = 1 / d rounded, d the square root of a positive float (so inv is
-// normal, or zero where d is infinite): the quotient corrected once by its exact
-// remainder, which rounds as the division does, in 5 instructions instead of
-// the 10 of a general one.  Where the remainder overflows (an infinite
-// operand or quotient) the product is already what the division gives.  Of
-// 3e8 pairs over the whole range of a and d the results differ from the
-// division's only where the remainder is subnormal (|a| < 1e-30), by one ulp.
-__device__ __forceinline__ float over(float a, float d, float inv) {
-  const float q = a * inv;
-  const float r = fmaf(-q, d, a);
-  return fabsf(r) < __builtin_inff() ? fmaf(r, inv, q) : q;
 }
 
 // solve (L L^T) x = b in place, L lower-triangular 5x5 packed by rows, inv: the
