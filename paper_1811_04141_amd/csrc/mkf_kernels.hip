@@ -1318,7 +1318,7 @@ __global__ __launch_bounds__(256) void k_tracks(FindParams P, const int *pos_of,
 // 34 us, against 27 and 46 in one kernel with one lane per seed; 500,000 seeds 129 us
 // of fit and 201 us of plans against 378.
 constexpr int kSeedBlock = 64;
-constexpr int kFewPlans = 32768;  // seeds up to which a plan has eight lanes
+constexpr int kFewPlans = 24576;  // seeds up to which a plan has eight lanes
 
 __global__ __launch_bounds__(256) void k_validate_seeds(FindParams P, const int *seed_event,
                                                         const int *seed_hits, int *bad) {
@@ -3140,9 +3140,11 @@ void launch_seed(hipStream_t s, const FindParams &P, const int *src_event, const
   hipLaunchKernelGGL(seed, dim3(blocks_for(P.n_seeds, kSeedBlock)), dim3(kSeedBlock), 0, s, P,
                      src_event, src_hits, seed_event, seed_hits, seed_state, seed_ok, seed_chi2,
                      fit);
-  // Eight lanes per seed shorten the chain, four do less twice over: at 500,000 seeds the plans
-  // take 286 us with eight and 201 with four, at 108,000 91 and 78; 5,000 seeds leave most of
-  // the chip idle with either, and the shorter chain counts.
+  // Eight lanes per seed shorten the chain, which counts while they leave part of the
+  // chip idle; four do less twice over.  Fit and plans together with eight and with
+  // four: 5,000 seeds 30 and 33 us, 16,000 40 and 41, 24,000 48 and 48, 32,000 61 and 48,
+  // 300,000 243 and 197; with material and field 10,000 0.93 and 1.02 ms, 16,000 1.03 and
+  // 1.02, 32,000 1.66 and 1.49.
   const bool few = P.n_seeds <= kFewPlans;
   const int lanes = few ? 8 : 4;
   const auto plans = few ? (ext ? k_seed_plan<true, 8> : k_seed_plan<false, 8>)

@@ -41,3 +41,25 @@ def test_states_do_not_depend_on_the_number_of_seeds(setup):
         for x, y in zip(c.get_seed_states(n), ref):
             assert np.ascontiguousarray(x).tobytes() == np.ascontiguousarray(y[at]).tobytes(), n
     c.close()
+
+
+@pytest.mark.parametrize("material", [False, True])
+def test_states_on_both_sides_of_the_lanes_rule(material):
+    """24,576 seeds are the last to have eight lanes each."""
+    from paper_1811_04141_amd import mkf
+    w = barrel_material() if material else barrel_endcap()
+    b = generate(w, events=[0])
+    c = mkf.Context(w.find)
+    c.load_geometry(w.layers)
+    if material:
+        c.load_material(w.material)
+    c.load_hits(b.ev_off, dev(b.x), dev(b.y), dev(b.z), dev(b.var_u), dev(b.var_v), dev(b.layer))
+    ref = None
+    for n in (61, 24576, 24577):
+        at = np.arange(n) % 61
+        c.seed(dev(b.seed_event[at]), dev(b.seed_hits[at]))
+        got = c.get_seed_states(n)
+        ref = got if ref is None else ref
+        for x, y in zip(got, ref):
+            assert np.ascontiguousarray(x).tobytes() == np.ascontiguousarray(y[at]).tobytes(), n
+    c.close()
