@@ -12,7 +12,6 @@
 #include <exception>
 #include <mutex>
 #include <new>
-#include <numeric>
 #include <string>
 #include <thread>
 #include <vector>
@@ -193,15 +192,18 @@ struct mkf_ctx {
 
   // fit scratch (host-side inputs are staged here)
   ~mkf_ctx() {
-    DevBuf *all[] = {&d_layers, &d_regions, &d_mat, &d_ev_off, &d_x, &d_y, &d_z, &d_vu, &d_vv, &d_layer,
-                     &d_bin_rank, &d_counts, &d_bin_start, &d_scan_tmp, &d_sorted,
+    DevBuf *all[] = {&d_layers, &d_regions, &d_mat, &d_ev_off, &d_x, &d_y, &d_z, &d_vu, &d_vv,
+                     &d_layer, &d_bin_rank, &d_counts, &d_bin_start, &d_scan_tmp, &d_sorted,
                      &d_byorig, &d_raw, &d_seed_event, &d_seed_hits, &d_seed_state, &d_seed_ok,
-                     &d_plan_len, &d_plan, &d_cell_counts, &d_cell_start, &d_cell_rank, &d_order, &d_pos, &d_pstate, &d_pinfo,
-                     &d_pevent, &d_pplan, &d_cand, &d_fin_key, &d_fin_rec, &d_fin_meta,
+                     &d_plan_len, &d_plan, &d_cell_counts, &d_cell_start, &d_cell_rank,
+                     &d_order, &d_pos, &d_pstate, &d_pinfo, &d_pevent, &d_pplan, &d_cand, &d_fin_key, &d_fin_rec, &d_fin_meta,
                      &d_bp, &d_out, &d_mlp_param, &d_mlp_m, &d_mlp_v, &d_W1p,
                      &d_W2p, &d_W3p, &d_W2T, &d_W3T, &d_mb1, &d_mb2, &d_mb3, &d_cnt, &d_radii,
-                     &d_tx, &d_tt, &d_tvalid, &d_partial, &d_partial2, &d_loss, &d_grad, &d_bf_tmp, &d_sm_wk, &d_sm_n, &d_tr_cnt, &d_tr_off, &d_tr_tmp, &d_tr_kept, &d_tr_at, &d_dup_h, &d_dup_n, &d_dup_cnt, &d_dup_off,
-                     &d_dup_fill, &d_dup_list, &d_dup_tmp, &d_dup_total, &d_clean_key, &d_seed_chi2, &d_seed_fit};
+                     &d_tx, &d_tt, &d_tvalid, &d_partial, &d_partial2, &d_loss, &d_grad,
+                     &d_bf_tmp, &d_sm_wk, &d_sm_n, &d_tr_cnt, &d_tr_off, &d_tr_tmp, &d_tr_kept,
+                     &d_tr_at, &d_dup_h, &d_dup_n, &d_dup_cnt, &d_dup_off, &d_dup_fill,
+                     &d_dup_list, &d_dup_tmp, &d_dup_total, &d_clean_key, &d_seed_chi2,
+                     &d_seed_fit};
     for (DevBuf *b : all) b->release();
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -764,8 +766,10 @@ mkf_status mkf_seed(mkf_ctx *c, int64_t n_seeds, const int32_t *seed_event,
     if (mem == MKF_MEM_DEVICE) {
       h_ev.resize(n_seeds);
       h_hits.resize(3 * n_seeds);
-      HIP_TRY(c, hipMemcpyAsync(h_ev.data(), seed_event, 4 * n_seeds, hipMemcpyDeviceToHost, c->stream));
-      HIP_TRY(c, hipMemcpyAsync(h_hits.data(), seed_hits, 12 * n_seeds, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(c, hipMemcpyAsync(h_ev.data(), seed_event, 4 * n_seeds, hipMemcpyDeviceToHost,
+                                c->stream));
+      HIP_TRY(c, hipMemcpyAsync(h_hits.data(), seed_hits, 12 * n_seeds, hipMemcpyDeviceToHost,
+                                c->stream));
       HIP_TRY(c, hipStreamSynchronize(c->stream));
       sev = h_ev.data();
       sh = h_hits.data();
@@ -897,13 +901,18 @@ mkf_status mkf_get_seed_states(mkf_ctx *c, float *par, float *cov, int32_t *ok,
 
 // Launch shape of the persistent find where none was set: as many waves per SIMD
 // as its tiles fill, from two up to three, the most that run without spilling
-// much (2 and 3 waves: 100 events x 5,000 seeds 1.79 and 1.39 ms, 24 such events
-// 0.427 and 0.371 ms, but 2 events 0.098 and 0.102 ms); four where that takes
-// all tiles at once (8 events, 4,000 tiles: 0.142 ms, 0.178 at three; 20 events
-// of 2,000 seeds with material and field 0.275 and 0.302 ms), though not with the
-// surrogate, which spills far more there.  No more blocks than are resident: the
-// starting value of eight per CU left the blocks beyond them to a second turn
-// (1.85 ms for 1.79 at two waves).
+// much; four where that takes all tiles at once, though not with the surrogate,
+// which spills far more there.  Measured at 18 numbers of tiles, events of 5,000
+// seeds, at two, three and four waves (us; on 1,024 SIMDs the lines are 2,048, 3,072
+// and 4,096 tiles):
+//   2,000 tiles 116, 118, 141    2,100  183, 124, 148   3,000  198, 128, 150
+//   3,100       202, 195, 166    4,090  203, 212, 172   4,150  252, 223, 240
+//   24,000      868, 684, 787
+//   with material and field  2,000  195, 207, 235   3,000 304, 218, 249
+//                            4,000  341, 341, 294   4,150 353, 349, 376
+//   with the surrogate       3,000  221, 147, 189   3,600 238, 233, 291
+// No more blocks than are resident: the starting value of eight per CU left the
+// blocks beyond them to a second turn (1.85 ms for 1.79 at two waves, 100 events).
 static void launch_shape(const mkf_ctx *c, int &waves, int &blocks_per_cu) {
   waves = c->tuning.waves_per_simd;
   blocks_per_cu = c->tuning.blocks_per_cu;
@@ -1067,7 +1076,8 @@ mkf_status mkf_get_tracks(mkf_ctx *c, mkf_track *out, int64_t capacity, int64_t 
     // records into slot k, which are then copied out
     auto work = [&](int k) {
       hipError_t e = k == 0 ? hipSuccess : hipSetDevice(c->device);
-      if (e == hipSuccess && !c->h_slot[k] && pin_records(&c->h_slot[k], kCopyRecords) != hipSuccess)
+      if (e == hipSuccess && !c->h_slot[k] &&
+          pin_records(&c->h_slot[k], kCopyRecords) != hipSuccess)
         return;  // no slot for this thread: the others take all chunks (the first has one)
       mkf_track *slot = c->h_slot[k];
       while (e == hipSuccess) {

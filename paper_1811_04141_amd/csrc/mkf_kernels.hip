@@ -171,7 +171,7 @@ struct Cand {
 // scattering angle constant.  The uniform form keeps the stepped crossing's and
 // the map's registers out of the kernel (fit 163 -> 112, backward tail 134 -> 110,
 // smoothing 204 -> 157, seeds 396 -> 310) and takes the angle's sine and cosine
-// once: 1 million fits of 26 hits 616 -> 575 us, backward fit of 500,000 tracks 436
+// once: 1 million fits of 26 hits 557 -> 511 us, backward fit of 500,000 tracks 436
 // -> 387 us (its FP64 part at two waves per SIMD, ten registers spilled; 414 at
 // one), 500,000 seeds 418 -> 378 us.
 template <bool kExt>
@@ -742,7 +742,8 @@ __device__ __forceinline__ int *write_state(const FindParams &P, int64_t pos, co
   for (int i = kOutMeta + 1; i < kOutHit; ++i) w[i] = 0.f;
 #pragma unroll
   for (int k = 0; k < kOutHit / 4; ++k)
-    reinterpret_cast<float4 *>(out)[k] = make_float4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
+    reinterpret_cast<float4 *>(out)[k] =
+        make_float4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
   return reinterpret_cast<int *>(out + kOutHit);
 }
 
@@ -1596,9 +1597,9 @@ __device__ __forceinline__ int bin_of(const DevLayer &L, float x, float y, float
 // (triplet_may_pass), and the lanes evaluate the few triplets left together.
 //
 // Bound by instruction issue in the walk over c (some 9 million candidates per
-// event of 5,000 tracks).  20 events x 5,000 tracks: 2.04 ms for the whole call,
-// against 51 ms with one lane per hit a and the FP64 cuts on every c, in two
-// passes.
+// event of 5,000 tracks).  20 events x 5,000 tracks: 2.0 ms for the whole call, of
+// which gathering 1.93, the cuts 0.042 and the placing 0.015, against 51 ms with one
+// lane per hit a and the FP64 cuts on every c, in two passes.
 
 // exact cuts of one triplet (FP64)
 __device__ __forceinline__ bool triplet_passes(const DevCfg &cfg, const DevSeeding &sc, double ax,
@@ -1750,8 +1751,8 @@ __device__ __forceinline__ int wave_inclusive(int v, int lane) {
 //     lane per triplet, and k_triplets_place puts those that pass in place.
 //     (With the cuts taken here, by the few lanes that hold a triplet, their
 //     FP64 arithmetic was half of the kernel's instructions and left it three
-//     waves per SIMD: 2.80 ms on 20 events x 5,000 tracks, where gathering takes
-//     2.05 at six waves per SIMD (2.30 at four) and the cuts 0.04.)
+//     waves per SIMD: 2.80 ms on 20 events x 5,000 tracks; gathering at four waves
+//     per SIMD took 2.30, at six it takes 1.93.)
 //   count, write: the same with the cuts, for the hits that did not fit.
 // A lane notes a few c per walk, and the walk is repeated where one has more: the
 // usual cuts leave few.  Loose ones leave hundreds, so gathering hands a hit over
@@ -2149,7 +2150,6 @@ __global__ __launch_bounds__(256) void k_dup_decide(FindParams P, const int *see
   if ((threadIdx.x & 63) == 0 && m != 0ull) atomicAdd(n_dup, (int)__popcll(m));
 }
 
-
 // -------------------------------------------------------- seed cleaning
 //
 // Seed cleaning (Section 2.2: seeds built from hits of the same outgoing
@@ -2346,7 +2346,8 @@ __global__ __launch_bounds__(256) void k_scan_sums(const int *in, int64_t n, int
   __shared__ int wsum[4];
   int v = 0;
   for (int t = 0; t < tiles; ++t) {
-    const int4 a = scan_load(in, ((int64_t)blockIdx.x * tiles + t) * kScanTile + 4 * threadIdx.x, n);
+    const int64_t k = ((int64_t)blockIdx.x * tiles + t) * kScanTile + 4 * threadIdx.x;
+    const int4 a = scan_load(in, k, n);
     v += a.x + a.y + a.z + a.w;
   }
   v = block_sum(v, wsum);
@@ -2579,8 +2580,8 @@ constexpr int kBfWords = 32;
 // through the track's first three hits in FP64 (they shrink it by ~5
 // decades, more than FP32 keeps in the covariance update).
 template <bool kExt>
-__global__ __launch_bounds__(kTrackBlock, kExt ? 1 : 2) void k_backfit_head(FindParams P, const int *seed_hits,
-                                                      float *tmp) {
+__global__ __launch_bounds__(kTrackBlock, kExt ? 1 : 2) void k_backfit_head(
+    FindParams P, const int *seed_hits, float *tmp) {
   __shared__ DevLayer sl[kMaxLayers];
   stage_layers(P, sl);
   __syncthreads();
@@ -2889,9 +2890,8 @@ __device__ __forceinline__ void chol_solve5(const float *Lp, const float *inv, f
 // lane, and each surface waits for LDS four times.  Two waves per SIMD: three
 // (153 registers) gain nothing on small calls, and on 2.5 M tracks of uneven
 // events their stores of single words to 64 rows meet in the L2 (4.08 against 4.01 ms).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_smooth_bwd(FindParams P, const float *wk,
-                                                    const int *n_surf, float *out_par,
-                                                    float *out_cov, int *out_n) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_smooth_bwd(
+    FindParams P, const float *wk, const int *n_surf, float *out_par, float *out_cov, int *out_n) {
   const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (pos >= P.n_seeds) return;
   const size_t N = (size_t)P.n_seeds;
@@ -3112,7 +3112,8 @@ void launch_hits_in(hipStream_t s, const FindParams &P, int64_t n_hits, const Hi
 void launch_scatter(hipStream_t s, const FindParams &P, int64_t n_hits, const int2 *bin_rank,
                     HitRec *sorted) {
   if (n_hits == 0) return;
-  hipLaunchKernelGGL(k_hit_scatter, dim3(blocks_for(n_hits, 256)), dim3(256), 0, s, P, n_hits, bin_rank, sorted);
+  hipLaunchKernelGGL(k_hit_scatter, dim3(blocks_for(n_hits, 256)), dim3(256), 0, s, P, n_hits,
+                     bin_rank, sorted);
 }
 
 void launch_scan(hipStream_t s, const int *in, int *out, int64_t n, int *tmp) {
@@ -3231,7 +3232,8 @@ void launch_find_persistent(hipStream_t s, const FindParams &P, int grid_blocks,
 void launch_finalize(hipStream_t s, const FindParams &P) {
   if (P.n_seeds == 0) return;
   const auto finalize = P.slots == 6 ? k_finalize<6> : k_finalize<8>;
-  hipLaunchKernelGGL(finalize, dim3(blocks_for(P.n_seeds, kTrackBlock)), dim3(kTrackBlock), 0, s, P);
+  hipLaunchKernelGGL(finalize, dim3(blocks_for(P.n_seeds, kTrackBlock)), dim3(kTrackBlock), 0, s,
+                     P);
 }
 void launch_check_results(hipStream_t s, const FindParams &P) {
   if (P.n_seeds == 0) return;
@@ -3273,8 +3275,8 @@ void launch_backfit(hipStream_t s, const FindParams &P, const int *seed_hits, fl
   const auto tail = ext ? k_backfit_tail<true> : k_backfit_tail<false>;
   const dim3 grid(blocks_for(P.n_seeds, kTrackBlock));
   hipLaunchKernelGGL(head, grid, dim3(kTrackBlock), 0, s, P, seed_hits, tmp);
-  hipLaunchKernelGGL(tail, grid, dim3(kTrackBlock), 0, s, P, seed_hits, tmp, out_par, out_cov, out_chi2,
-                     out_status);
+  hipLaunchKernelGGL(tail, grid, dim3(kTrackBlock), 0, s, P, seed_hits, tmp, out_par, out_cov,
+                     out_chi2, out_status);
 }
 
 void launch_smooth(hipStream_t s, const FindParams &P, const int *seed_hits, float *wk,
@@ -3329,18 +3331,18 @@ void launch_triplets_write(hipStream_t s, const FindParams &P, const DevSeeding 
                            int64_t n_hits, int64_t max_event_hits, int *counts, const int *offsets,
                            const TripletStore &st, bool again, int *out_event, int *out_hits) {
   if (max_event_hits == 0 || P.n_events == 0) return;
-  hipLaunchKernelGGL(k_triplets_place, triplet_grid(P, n_hits, max_event_hits, 32), dim3(256), 0, s, P, sc,
-                     counts, offsets, st, out_event, out_hits);
+  hipLaunchKernelGGL(k_triplets_place, triplet_grid(P, n_hits, max_event_hits, 32), dim3(256), 0, s,
+                     P, sc, counts, offsets, st, out_event, out_hits);
   if (again)
-    hipLaunchKernelGGL(k_triplets<kWriteOut>, triplet_grid(P, n_hits, max_event_hits, 4), dim3(256), 0, s,
-                       P, sc, counts, offsets, st, out_event, out_hits);
+    hipLaunchKernelGGL(k_triplets<kWriteOut>, triplet_grid(P, n_hits, max_event_hits, 4),
+                       dim3(256), 0, s, P, sc, counts, offsets, st, out_event, out_hits);
 }
 
 void launch_dup_prep(hipStream_t s, const FindParams &P, const int *seed_hits, int *hbuf, int *hn,
                      int *cnt) {
   if (P.n_seeds == 0) return;
-  hipLaunchKernelGGL(k_dup_prep, dim3(blocks_for(P.n_seeds, kDupBlock)), dim3(kDupBlock), 0, s, P, seed_hits,
-                     hbuf, hn, cnt);
+  hipLaunchKernelGGL(k_dup_prep, dim3(blocks_for(P.n_seeds, kDupBlock)), dim3(kDupBlock), 0, s, P,
+                     seed_hits, hbuf, hn, cnt);
 }
 
 void launch_dup_fill(hipStream_t s, const FindParams &P, const int *hbuf, const int *hn,

@@ -52,7 +52,8 @@ struct FindParams {
   // hits
   int n_events;
   const int64_t *ev_off;   // n_events + 1
-  const float2 *raw;       // the caller's variances, or null where vu, vv are they (no stereo layer)
+  const float2 *raw;       // the caller's variances, or null where vu, vv are they (no stereo
+                           // layer)
   const HitRec *sorted;    // binned
   const HitRec *byorig;    // the same records in the caller's order, all events
   const int *bin_start;    // n_events * bins_per_event + 1

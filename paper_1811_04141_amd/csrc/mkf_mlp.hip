@@ -167,9 +167,11 @@ __device__ __forceinline__ void tile_store(const f32x16 &acc, __bf16 *sm, int ld
 __global__ __launch_bounds__(256) void k_mlp_grad(GradParams G) {
   __shared__ __attribute__((aligned(16))) __bf16 sX[64 * kLdX];
   __shared__ __attribute__((aligned(16))) __bf16 sXu[32 * kLdU];
-  __shared__ __attribute__((aligned(16))) __bf16 sH1[64 * kLdH], sH1u[64 * kLdU], sH2[64 * kLdH], sH2u[64 * kLdU];
+  __shared__ __attribute__((aligned(16))) __bf16 sH1[64 * kLdH], sH1u[64 * kLdU];
+  __shared__ __attribute__((aligned(16))) __bf16 sH2[64 * kLdH], sH2u[64 * kLdU];
   __shared__ __attribute__((aligned(16))) __bf16 sDY[64 * kLdY], sDYu[32 * kLdU];
-  __shared__ __attribute__((aligned(16))) __bf16 sDZ2[64 * kLdH], sDZ2u[64 * kLdU], sDZ1u[64 * kLdU];
+  __shared__ __attribute__((aligned(16))) __bf16 sDZ2[64 * kLdH], sDZ2u[64 * kLdU];
+  __shared__ __attribute__((aligned(16))) __bf16 sDZ1u[64 * kLdU];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
   const int wv = tid >> 6, mt = wv >> 1, nt = wv & 1;
   const int64_t base = G.begin + (int64_t)blockIdx.x * 64;
@@ -180,7 +182,8 @@ __global__ __launch_bounds__(256) void k_mlp_grad(GradParams G) {
   typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
   float4_any xin = {0.f, 0.f, 0.f, 0.f};
   if (tid < 128)
-    xin = *reinterpret_cast<const float4_any *>(G.x + ((base + (tid >> 1)) % G.n) * 8 + 4 * (tid & 1));
+    xin = *reinterpret_cast<const float4_any *>(G.x + ((base + (tid >> 1)) % G.n) * 8 +
+                                                4 * (tid & 1));
   float tgt[4] = {}, vld = 0.f;
   if (wv < 2) {
     const int64_t sj = (base + 32 * nt + r) % G.n;
@@ -230,7 +233,8 @@ __global__ __launch_bounds__(256) void k_mlp_grad(GradParams G) {
     f32x16 a;
 #pragma unroll
     for (int i = 0; i < 16; ++i) a[i] = silu(z1[i]);
-    tile_store<true, true>(a, sH1 + 32 * nt * kLdH + 32 * mt, kLdH, sH1u + 32 * mt * kLdU + 32 * nt);
+    tile_store<true, true>(a, sH1 + 32 * nt * kLdH + 32 * mt, kLdH,
+                           sH1u + 32 * mt * kLdU + 32 * nt);
   }
   __syncthreads();
   const f32x16 z2 = tile_mma(w2, sH1 + 32 * nt * kLdH, kLdH, c2);
@@ -238,7 +242,8 @@ __global__ __launch_bounds__(256) void k_mlp_grad(GradParams G) {
     f32x16 a;
 #pragma unroll
     for (int i = 0; i < 16; ++i) a[i] = silu(z2[i]);
-    tile_store<true, true>(a, sH2 + 32 * nt * kLdH + 32 * mt, kLdH, sH2u + 32 * mt * kLdU + 32 * nt);
+    tile_store<true, true>(a, sH2 + 32 * nt * kLdH + 32 * mt, kLdH,
+                           sH2u + 32 * mt * kLdU + 32 * nt);
   }
   __syncthreads();
   float loss = 0.f;
